@@ -18,10 +18,10 @@
 //    neighbour slots sorted by the neighbour's layer: at step k the neighbours
 //    whose X^(k-1) is non-zero form a prefix of that list.
 //  * The steps are step-synchronous launches over a batch of tiles; a
-//    wavefront owns a row and all 64 columns.  The row's H blocks reach the
-//    wave's LDS slice by an asynchronous copy issued after the previous row
-//    (FP32), or are read with scalar loads (FP64); neighbour rows of X^(k-1)
-//    are coalesced vector loads in double-buffered groups; X^k is written with
+//    wavefront owns a row and all 64 columns.  FP64 reads the row's H blocks with
+//    scalar loads and multiplies on the VALU (k_step); FP32 multiplies on
+//    4x4x1 MFMA, the blocks loaded once per wave (k_step32).  Neighbour rows of
+//    X^(k-1) are coalesced 16-byte loads per lane; X^k is written with
 //    non-temporal stores.  Blocks are numbered so that all chunks of a tile run
 //    on one XCD (block b runs on XCD b mod 8) one tile after another, and the
 //    rows are dealt to the tile's chunks in wave-sized groups round robin, so
@@ -36,6 +36,8 @@
 //    last step, so results are deterministic for a given plan.
 #include "bop_internal.h"
 #include "tiles.h"
+
+#include <type_traits>
 
 namespace bop {
 namespace {
@@ -605,11 +607,95 @@ k_prepare(int n_atoms, int B, int n_tiles, int K, const int *__restrict__ order,
 // ---------------------------------------------------------------------------
 // moments: X^0, steps, reductions
 // ---------------------------------------------------------------------------
-template <typename T> __device__ inline T from_f64(double v) { return (T)v; }
-
 struct Batch {
     int first, count;          // tiles [first, first + count)
 };
+
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+constexpr int AUX_NT = 2;           // non-temporal bit of a buffer access
+
+// Layout of a row of X (64 columns, one per lane): the orbitals are grouped into
+// planes of V values per lane, so that a lane reads or writes its column's
+// values of a row with one wide access per plane (16 bytes for FP64 and FP32)
+// instead of one per orbital; the orbital left over has a plane of its own.
+template <typename S, int NO> struct XRow {
+    static constexpr int V = sizeof(S) >= 4 ? 16 / (int)sizeof(S) : NO - 1;
+    static constexpr int NP = NO / V, TAIL = NP * V * 64;
+    static_assert(NO - NP * V == 1, "one orbital is left over");
+    typedef S vec __attribute__((ext_vector_type(V)));
+    // element of orbital a, column c
+    static __host__ __device__ int at(int a, int c) { return a < NP * V ? (a / V) * V * 64 + c * V + a % V : TAIL + c; }
+    template <bool NT, typename T> static __device__ inline void load(const S *row, int lane, T (&x)[NO])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const vec *q = (const vec *)(row + p * V * 64) + lane;
+            const vec v = NT ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+            for (int e = 0; e < V; ++e) x[p * V + e] = (T)v[e];
+        }
+        const S *q = row + TAIL + lane;
+        x[NO - 1] = (T)(NT ? __builtin_nontemporal_load(q) : *q);
+    }
+    // non-temporal
+    static __device__ inline void store(S *row, int lane, const S (&x)[NO])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            vec v;
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = x[p * V + e];
+            __builtin_nontemporal_store(v, (vec *)(row + p * V * 64) + lane);
+        }
+        __builtin_nontemporal_store(x[NO - 1], row + TAIL + lane);
+    }
+    // The same through a buffer descriptor of the row: its base is wave-uniform, so
+    // that addresses cost no vector instruction, and one of no bytes (on false) reads
+    // zeros and drops stores without a branch, which would hide the number of
+    // accesses in flight from the waits that follow it.
+    static __device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const S *row, bool on)
+    {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, on ? NO * 64 * (int)sizeof(S) : 0, 0x00027000);
+    }
+    template <int AUX, typename T> static __device__ inline void load(__amdgpu_buffer_rsrc_t r, int lane, T (&x)[NO])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            vec v;
+            if constexpr (sizeof(vec) == 16)
+                v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + p * 1024, 0, AUX));
+            else v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(r, lane * 8 + p * 512, 0, AUX));
+#pragma unroll
+            for (int e = 0; e < V; ++e) x[p * V + e] = (T)v[e];
+        }
+        if constexpr (sizeof(S) == 8)
+            x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+        else if constexpr (sizeof(S) == 4)
+            x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+        else x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+    }
+    // non-temporal
+    static __device__ inline void store(__amdgpu_buffer_rsrc_t r, int lane, const S (&x)[NO])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            vec v;
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = x[p * V + e];
+            if constexpr (sizeof(vec) == 16)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, lane * 16 + p * 1024, 0, AUX_NT);
+            else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, lane * 8 + p * 512, 0, AUX_NT);
+        }
+        if constexpr (sizeof(S) == 8)
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
+        else if constexpr (sizeof(S) == 4)
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
+        else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
+    }
+};
+
 
 // X^0 = unit columns on the seed rows; mu_0 = 1 (NaN moments for failed tiles)
 template <typename T, int NO>
@@ -633,7 +719,7 @@ __global__ void k_x0(Batch bt, int n_max, int B, const int *__restrict__ sizes_,
     T *X0 = (T *)(xbase + x_stride * (2 * (size_t)t));
     for (int e = threadIdx.x; e < Bt * NO * 64; e += blockDim.x) {
         int l = e / (NO * 64), rest = e % (NO * 64), a = rest / 64, c = rest % 64;
-        X0[(long)l * NO * 64 + a * 64 + c] = (c == l * NO + a) ? T(1) : T(0);
+        X0[(long)l * NO * 64 + XRow<T, NO>::at(a, c)] = (c == l * NO + a) ? T(1) : T(0);
     }
     for (int e = threadIdx.x; e < Bt * NO; e += blockDim.x) {
         int b = e / NO, a = e % NO;
@@ -641,20 +727,11 @@ __global__ void k_x0(Batch bt, int n_max, int B, const int *__restrict__ sizes_,
     }
 }
 
-// Asynchronous copy of n floats from global memory into an LDS slice
-// (global_load_lds: lane i's dword lands at the slice base + 4 i for every
-// 64-float chunk); completion is counted by vmcnt like any vector load.
-__device__ inline void h_to_lds(const float *src, float *dst, int n, int lane)
-{
-    for (int e = 0; e < n; e += 64)
-        if (e + lane < n)
-            __builtin_amdgcn_global_load_lds((const void *)(src + e + lane),
-                                             (__attribute__((address_space(3))) void *)(dst + e), 4, 0, 0);
-}
-
-// The same copy 16 bytes per lane (global_load_lds_dwordx4: lane i's 16 bytes
-// land at the slice base + 16 i for every 256-float chunk); n a multiple of 4,
-// src and dst 16-byte aligned.  One instruction moves 1 KB.
+// Asynchronous copy of n floats from global memory into an LDS slice, 16 bytes
+// per lane (global_load_lds_dwordx4: lane i's 16 bytes land at the slice base +
+// 16 i for every 256-float chunk); n a multiple of 4, src and dst 16-byte
+// aligned.  One instruction moves 1 KB; completion is counted by vmcnt like any
+// vector load.
 __device__ inline void h_to_lds16(const float *src, float *dst, int n, int lane)
 {
     for (int e = 0; e < n; e += 256)
@@ -671,19 +748,17 @@ template <typename T> __device__ inline const __attribute__((address_space(4))) 
     return (const __attribute__((address_space(4))) T *)p;
 }
 
-// Floats of one wave's LDS slice of H blocks (deg_max blocks, whole 64-float
-// chunks so that the copy never writes past it).
-__host__ __device__ inline int h_slice(int deg_max, int nb) { return (deg_max * nb + 63) / 64 * 64; }
-
 // One step (or the final odd H X^K pass) for a batch of tiles.
-// Latency structure: the H blocks of a wave's next row (one contiguous range
-// of pairs) are copied into its LDS slice asynchronously as soon as the
-// current row's products are done, so they arrive with the next row's first
-// gathers; the X gathers of G neighbour slots are issued before any of them is
-// used, so a row costs a few memory round trips instead of one per slot.  X^k
-// is written with non-temporal stores: it is read only by the next launch,
-// long after it would have left L2, where it would evict the rows being
-// gathered.
+// FP64 form (k_step32 is the FP32 one).  The H blocks are read with scalar loads
+// into SGPR operands from their wave-uniform addresses (11-34% faster than LDS
+// copies here); the X gathers of G neighbour slots are issued before any of them
+// is used.  X^k is written with non-temporal stores: it is read only by the next
+// launch, long after it would have left L2, where it would evict the rows being
+// gathered.  With one 16-byte access per lane and orbital pair (XRow) instead of
+// one 8-byte access per orbital a row takes three vector memory instructions
+// where it took five: 128,000 atoms, 18 moments 338 -> 289 ms (4.6 TB gathered,
+// bound by the rate at which L1 returns them: the time follows the number of
+// accesses, not the VALU's 23%).
 //
 // LANCZOS = 1: one whole Lanczos level j = k - 1 per pass (the support of
 // H u_j is that of X^k).  A tile then has four vectors: Y (two, ping-pong) and
@@ -699,28 +774,325 @@ __host__ __device__ inline int h_slice(int deg_max, int nb) { return (deg_max * 
 // k_lreduce_fused takes a_j = s_j <r_j, y'_(j+1)> and b_(j+1)^2 = |y'_(j+1) -
 // a_j u_j|^2 = |y'|^2 - 2 a_j^2 + a_j^2 s_j^2 |r_j|^2.  Per column (lane) lc
 // gives s_j, beta_j = b_j s_(j-1), c_j, beta_(j-1) and 1/s_(j-1).
-template <typename T, int NO, int WGT, int LANCZOS, typename S = T, bool HS = false, bool TR = false>
+template <int NO, int WGT, int LANCZOS, bool TR>
 __global__ void __launch_bounds__(WGT)
-k_step(Batch bt, int k, int K, int last, int keep, int fin, int nch, int chunk_rows, int deg_max, int rows_cap,
-       const int *__restrict__ row_ptr, const double *__restrict__ H_on, const T *__restrict__ H,
+k_step(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, int deg_max, int rows_cap,
+       const int *__restrict__ row_ptr, const double *__restrict__ H_on, const double *__restrict__ H,
        const int *__restrict__ sizes_, const char *tiles_base, size_t tile_stride, char *xbase,
        size_t x_stride, double *__restrict__ part, const double *__restrict__ lc)
 {
     constexpr int NW = WGT / 64;
+    using T = double;
+    using XR = XRow<double, NO>;
     // values per H block: d-d blocks are stored packed (symmetric, upper
     // triangle), s,p,d blocks in full
     constexpr int NB = NO == 5 ? BOP_D_PACKED : NO * NO;
-    // Slots whose gathers are in flight together.  Occupancy decides the step:
-    // FP32 takes groups of 2 slots, double-buffered (the next group's gathers
-    // are issued before the current one is multiplied), which keeps the d
-    // kernel at 59 VGPRs (8 waves per SIMD) and measured 3% faster than single
-    // groups of 4 and 8% faster than double-buffered groups of 4 (6 waves);
-    // FP64 rows are two or four times wider, and single groups of 2 (d) or
-    // 1 (s,p,d) slots measured fastest there.
-    constexpr bool PIPE = sizeof(T) == 4;
-    constexpr int G = sizeof(T) == 8 ? (NO <= 5 ? 2 : 1) : 2;
+    constexpr int G = NO <= 5 ? 2 : 1;          // slots whose gathers are in flight together
     __shared__ double s_red[LANCZOS ? 3 : 2][NW][64];
-    extern __shared__ char s_dyn[];
+    // XCD-aware numbering: block b runs on XCD b % 8; the other factor walks
+    // tile-major through (tile, chunk)
+    const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+    const int t = (q / nch) * 8 + xcd, chunk = q % nch;
+    if (t >= bt.count) return;
+    const int tile = bt.first + t;
+    const int *sizes = sizes_ + tile * (MAXK + 2);
+    if (sizes[0] < 0) return;
+    const int nrow = last ? sizes[K] : sizes[k];
+    const int nct = tile_chunks(nrow, chunk_rows, NW);
+    if (chunk >= nct) return;
+    const int RS = nct * NW;                                 // row stride of this chunk
+    const int *sup = (const int *)(tiles_base + tile_stride * tile);
+    const int *rinfo = sup + rows_cap;
+    const int *lnb = rinfo + rows_cap;
+    const int *rmask = lnb + (long)rows_cap * deg_max;   // path radius: tile atoms that keep the row
+    const int src = last ? (K & 1) : ((k - 1) & 1);
+    constexpr size_t NBUF = LANCZOS ? 4 : 2;      // X buffers per tile
+    const T *Xp = (const T *)(xbase + x_stride * (NBUF * t + src));
+    T *Xc = (T *)(xbase + x_stride * (NBUF * t + (k & 1)));
+    // Lanczos: r_(j-2) read and r_j written (same buffer), r_(j-1) read
+    T *Ra = (T *)(xbase + x_stride * (NBUF * t + 2 + ((k - 1) & 1)));
+    const T *Rb = (const T *)(xbase + x_stride * (NBUF * t + 2 + (k & 1)));
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int stride_row = NO * 64;
+    double so = 0.0, se = 0.0, sx = 0.0;
+    T ls = T(1), lbeta = T(0), lcj = T(0), lbp = T(0), linv = T(0);
+    if (LANCZOS) {
+        const double *l = lc + (size_t)t * LC_N * 64 + lane;
+        ls = (T)l[0];
+        lbeta = (T)l[64];
+        lcj = (T)l[128];
+        lbp = (T)l[192];
+        linv = (T)l[256];
+    }
+    // the next row's atom, layer word, slot list and pair range are fetched while
+    // the current row computes, which takes their dependent loads off the
+    // critical path
+    int l = chunk * NW + w;
+    int g_n = 0, info_n = 0, slots_n = 0, p0_n = 0, tm_n = -1;
+    if (l < nrow) {
+        g_n = cst(sup)[l];
+        info_n = cst(rinfo)[l];
+        if constexpr (TR) tm_n = cst(rmask)[l];
+        slots_n = lane < deg_max ? lnb[(long)l * deg_max + lane] : 0;
+        p0_n = cst(row_ptr)[g_n];
+    }
+    for (; l < nrow; l += RS) {
+        const int g = g_n, info = info_n, slots_all = slots_n, p0 = p0_n, tm = tm_n;
+        if (l + RS < nrow) {
+            g_n = cst(sup)[l + RS];
+            info_n = cst(rinfo)[l + RS];
+            if constexpr (TR) tm_n = cst(rmask)[l + RS];
+            slots_n = lane < deg_max ? lnb[(long)(l + RS) * deg_max + lane] : 0;
+            p0_n = cst(row_ptr)[g_n];
+        }
+        const int L = info & 255, n1 = (info >> 8) & 255, n2 = (info >> 16) & 255, n3 = (info >> 24) & 255;
+        const bool has_prev = last || L <= k - 1;
+        const int nval = last ? n3 : (k - 1 >= L + 1 ? n3 : (k - 1 == L ? n2 : n1));
+        const int slots = (lane < nval) ? slots_all : 0;
+        const T *hsrc = H + (long)p0 * NB;
+        const T *xrow = Xp + (long)l * stride_row;
+        T acc[NO], xs[NO] = {};
+        if (has_prev) XR::template load<false>(xrow, lane, xs);
+#pragma unroll
+        for (int a = 0; a < NO; ++a) acc[a] = cst(H_on)[(long)g * NO + a] * xs[a];
+        // gather a group of G slots (slots past nval re-read this row, harmless,
+        // and are masked in the product)
+        auto gather = [&](int s0, T (&x)[G][NO], int (&hoff)[G]) {
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const int su = s0 + u < nval ? s0 + u : 0;
+                const int pk = __builtin_amdgcn_readlane(slots, su);
+                const T *xn = (s0 + u < nval) ? Xp + (long)(pk >> 8) * stride_row : xrow;
+                hoff[u] = (pk & 255) * NB;
+                XR::template load<false>(xn, lane, x[u]);
+            }
+        };
+        auto product = [&](int s0, const T (&x)[G][NO], const int (&hoff)[G]) {
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                if (s0 + u < nval) {
+                    const T *h = hsrc + hoff[u];
+#pragma unroll
+                    for (int a = 0; a < NO; ++a)
+#pragma unroll
+                        for (int b = 0; b < NO; ++b)
+                            acc[a] = fma(h[NO == 5 ? d_packed_index(a, b) : a * NO + b], x[u][b], acc[a]);
+                }
+            }
+        };
+        for (int s0 = 0; s0 < nval; s0 += G) {
+            T x[G][NO];
+            int hoff[G];
+            gather(s0, x, hoff);
+            product(s0, x, hoff);
+        }
+        // path radius: a column keeps the row only within r_max of its atom
+        if constexpr (TR) {
+            if (!((tm >> (lane / NO)) & 1)) {
+#pragma unroll
+                for (int a = 0; a < NO; ++a) acc[a] = T(0);
+            }
+        }
+        (void)tm;
+        T *xo = Xc + (long)l * stride_row;
+        if constexpr (LANCZOS) {
+            // the row's own r_(j-1) and r_(j-2) (zero outside their supports),
+            // loaded after the products so that they hold no registers there;
+            // read once, so non-temporal loads keep them from displacing the
+            // gathered rows in L2 (1% on the FP32 pass)
+            const bool h1 = L <= k - 2, h2 = L <= k - 3;
+            const long off = (long)l * stride_row;
+            T r1[NO] = {}, r2[NO] = {}, rw[NO], yw[NO];
+            if (h1) XR::template load<true>(Rb + off, lane, r1);
+            if (h2) XR::template load<true>(Ra + off, lane, r2);
+#pragma unroll
+            for (int a = 0; a < NO; ++a) {
+                const T hrp = (xs[a] + lbp * r2[a]) * linv;      // H r_(j-1) at this row
+                const T hr = acc[a] - lcj * hrp;                 // H r_j
+                const T rj = xs[a] - lcj * r1[a];                // r_j
+                const T y = ls * hr - lbeta * r1[a];             // y'_(j+1)
+                rw[a] = rj;
+                yw[a] = y;
+                so = fma(rj, y, so);
+                se = fma(y, y, se);
+                sx = fma(rj, rj, sx);
+            }
+            // r_j is zero on the newest layer (L = k, where y'_j and r_(j-1) are)
+            // and no later pass reads it there: stored on the older layers only
+            if (keep) {
+                if (has_prev) XR::store(Ra + off, lane, rw);
+                XR::store(xo, lane, yw);
+            }
+        } else {
+            if (keep) XR::store(xo, lane, acc);
+#pragma unroll
+            for (int a = 0; a < NO; ++a) {
+                so = fma(xs[a], acc[a], so);
+                se = fma(acc[a], acc[a], se);
+            }
+        }
+    }
+    s_red[0][w][lane] = so;
+    s_red[1][w][lane] = se;
+    if constexpr (LANCZOS) s_red[2][w][lane] = sx;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        double to = 0.0, te = 0.0, tx = 0.0;
+#pragma unroll
+        for (int q2 = 0; q2 < NW; ++q2) {
+            to += s_red[0][q2][threadIdx.x];
+            te += s_red[1][q2][threadIdx.x];
+            if constexpr (LANCZOS) tx += s_red[2][q2][threadIdx.x];
+        }
+        constexpr int ns = LANCZOS ? 3 : 2;
+        double *pp = part + (((size_t)t * nch + chunk) * ns) * 64;
+        pp[threadIdx.x] = to;
+        pp[64 + threadIdx.x] = te;
+        if constexpr (LANCZOS) pp[128 + threadIdx.x] = tx;
+    }
+}
+
+// compile-time loop: f(integral_constant<int, I>) for I = 0 .. N-1
+template <int N, int I = 0, typename F> __device__ inline void static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
+}
+
+// acc += (lane K of every 16-lane row of h) * x.  A broadcasting operand costs
+// no instruction of its own.  The operand may not be read within two waits of
+// a VALU write; callers pass h as loaded, with dpp_guard() before the first use.
+template <int K> __device__ inline void fma_bcast(float &acc, float h, float x)
+{
+    asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(h), "v"(x), "n"(K));
+}
+__device__ inline void dpp_guard(float &h) { asm("s_nop 1" : "+v"(h)); }
+
+// One neighbour block's product acc[a] += sum_b H[a][b] x[b] over the 64
+// columns (one per lane), b inner, each term one fused multiply-add: the block
+// is loaded once per wave in the lanes where the instructions read it (NR
+// registers; off(i, lane) is the element of the block lane reads into register i).
+//
+// FP32: orbitals a = 4q .. 4q+3 on v_mfma_f32_4x4x1_16b: A holds 16 columns of
+// four values (lanes 4j .. 4j+3), one of them broadcast to all 16 column blocks,
+// B is the lane's x[b] and D[r] the lane's acc[4q + r], so no operand moves
+// between lanes; a K = 1 product rounds like fma().  It runs at twice the VALU's
+// rate and beside it; the last orbital stays on the VALU with the block's last
+// row broadcast from each 16-lane row.  d: column b in A column 4b (b < 4) or 1,
+// the last row in lanes 8 .. 12 of each row.  s,p,d: columns (b, q) at 2b + q, b
+// < 8, in register 0; register 1 has b = 8 in columns 0 and 4 and the last row in
+// lanes 4 .. 12.
+template <int NO> struct Block;
+
+template <> struct Block<5> {
+    static constexpr int NR = 1;
+    static __device__ inline int off(int, int lane)
+    {
+        const int r = lane >> 4, p = lane & 15;
+        if (p < 4) return d_packed_index(p, r);
+        if (p < 8) return d_packed_index(p - 4, 4);
+        return p < 13 ? d_packed_index(4, p - 8) : 15;
+    }
+    static __device__ inline void mul(float (&h)[NR], const float (&x)[5], f32x4_t (&q)[1], float &tail)
+    {
+        dpp_guard(h[0]);
+        static_for<5>([&](auto b) {
+            constexpr int B = decltype(b)::value;
+            q[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(h[0], x[B], q[0], 4, B < 4 ? 4 * B : 1, 0);
+            fma_bcast<8 + B>(tail, h[0], x[B]);
+        });
+    }
+};
+
+template <> struct Block<9> {
+    static constexpr int NR = 2;
+    static __device__ inline int off(int i, int lane)
+    {
+        const int r = lane >> 4, p = lane & 15, j = lane >> 2, m = lane & 3;
+        if (i == 0) return (4 * (j & 1) + m) * 9 + (j >> 1);
+        if (p < 4) return (4 * (r & 1) + p) * 9 + 8;
+        return 72 + (p < 13 ? p - 4 : 0);
+    }
+    static __device__ inline void mul(float (&h)[NR], const float (&x)[9], f32x4_t (&q)[2], float &tail)
+    {
+        dpp_guard(h[1]);
+        static_for<9>([&](auto b) {
+            constexpr int B = decltype(b)::value;
+            if constexpr (B < 8) {
+                q[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(h[0], x[B], q[0], 4, 2 * B, 0);
+                q[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(h[0], x[B], q[1], 4, 2 * B + 1, 0);
+            } else {
+                q[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(h[1], x[B], q[0], 4, 0, 0);
+                q[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(h[1], x[B], q[1], 4, 4, 0);
+            }
+            fma_bcast<4 + B>(tail, h[1], x[B]);
+        });
+    }
+};
+
+// A row's accumulators in the form its products want them.
+template <int NO> struct Acc {
+    f32x4_t q[NO / 4];
+    float tail;
+    __device__ inline void start(const float (&e)[NO])
+    {
+#pragma unroll
+        for (int a = 0; a < NO - 1; ++a) q[a / 4][a % 4] = e[a];
+        tail = e[NO - 1];
+    }
+    __device__ inline void get(float (&o)[NO]) const
+    {
+#pragma unroll
+        for (int a = 0; a < NO - 1; ++a) o[a] = q[a / 4][a % 4];
+        o[NO - 1] = tail;
+    }
+};
+
+// the value is formed here, in a register of its own
+template <typename T> __device__ inline void pin(T &v) { asm volatile("" : "+v"(v)); }
+
+
+
+// Rows of up to this many pairs pass their H blocks through LDS (HL): 64 lanes of
+// 16 bytes fetch them all.
+constexpr int HL_PAIRS = 16;
+// slots of a row whose words are held in scalar registers from a row ahead
+constexpr int SLOTS_HELD = 16;
+
+// The same step (k_step: rows, sums and their order are its own) for FP32, and for
+// vectors stored in FP16 (S).  What bounds it is the traffic between L2 and memory
+// (about 3.7 TB/s in every variant) and, for s,p,d, the rate of L1 accesses; so the
+// products leave the VALU (60% busy before, 27% now), and what a wave waits for is
+// asked for early: a row's records two rows ahead, its vectors before the stores of
+// the row before it.  Against products on the VALU from LDS copies of the blocks,
+// 18 moments: s,p,d Lanczos, 6,912 atoms 95.3 -> 68.6 ms; FP16 rows, 2,048 atoms
+// 24.2 -> 11.4 ms; d moments, 128,000 atoms 154.5 -> 141.8 ms, d Lanczos 205.5 ->
+// 204.2 ms, all results bit-identical.  Five slots in flight for d (four, six and
+// seven within 1%), two for s,p,d (three 2% slower, one 20%).
+//
+// HL: a row of up to HL_PAIRS pairs fetches its d blocks with one 16-byte load per
+// lane and passes them through LDS, which takes an eighth of the L1 accesses of
+// loading each block in the products' order (31.1 against 35.6 ms, d moments,
+// 27,648 atoms); longer rows and s,p,d (whose blocks would take six such loads and
+// 24 registers) load block by block.
+template <int NO, int WGT, int LANCZOS, typename S, bool HL, bool TR>
+__global__ void __launch_bounds__(WGT) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_step32(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, int deg_max, int rows_cap,
+       const int *__restrict__ row_ptr, const double *__restrict__ H_on, const float *__restrict__ H,
+       const int *__restrict__ sizes_, const char *tiles_base, size_t tile_stride, char *xbase,
+       size_t x_stride, double *__restrict__ part, const double *__restrict__ lc)
+{
+    constexpr int NW = WGT / 64;
+    constexpr int NB = NO == 5 ? BOP_D_PACKED : NO * NO;
+    constexpr int NS = NO == 5 ? 5 : 2;         // slots whose gathers are in flight together
+    constexpr int NR = Block<NO>::NR;
+    using T = float;
+    using XR = XRow<S, NO>;
+    __shared__ double s_red[LANCZOS ? 3 : 2][NW][64];
+    __shared__ __align__(16) float s_h[HL ? NW : 1][HL ? HL_PAIRS * NB : 4];     // a row's H blocks
     // XCD-aware numbering: block b runs on XCD b % 8; the other factor walks
     // tile-major through (tile, chunk)
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
@@ -746,8 +1118,10 @@ k_step(Batch bt, int k, int K, int last, int keep, int fin, int nch, int chunk_r
     const S *Rb = (const S *)(xbase + x_stride * (NBUF * t + 2 + (k & 1)));
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    T *sH = (T *)s_dyn + (size_t)w * h_slice(deg_max, NB);  // this wave's H blocks
     constexpr int stride_row = NO * 64;
+    unsigned hoff[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) hoff[i] = (unsigned)sizeof(T) * Block<NO>::off(i, lane);
     double so = 0.0, se = 0.0, sx = 0.0;
     T ls = T(1), lbeta = T(0), lcj = T(0), lbp = T(0), linv = T(0);
     if (LANCZOS) {
@@ -758,150 +1132,136 @@ k_step(Batch bt, int k, int K, int last, int keep, int fin, int nch, int chunk_r
         lbp = (T)l[192];
         linv = (T)l[256];
     }
-    // a row's H blocks into the LDS slice: 16 bytes per lane where every block
-    // is a whole number of 16-byte units (packed FP32 d-d blocks, 64 bytes)
-    auto h_copy = [&](const float *src, float *dst, int n) {
-        if constexpr (sizeof(T) == 4 && (NB * sizeof(T)) % 16 == 0) h_to_lds16(src, dst, n, lane);
-        else h_to_lds(src, dst, n, lane);
+    // What a row's pass needs to know of it, by scalar loads a row ahead of their
+    // use (the atom, whose pair range takes a second load, two rows ahead).
+    struct Rec { int atom, info, mask, p0, p1, word[SLOTS_HELD]; };
+    auto atom_of = [&](int l) { return cst(sup)[min(l, nrow - 1)]; };
+    auto record = [&](int l, int atom, Rec &m) {
+        const int lc = min(l, nrow - 1);
+        m.atom = atom;
+        m.info = cst(rinfo)[lc];
+        m.mask = TR ? cst(rmask)[lc] : -1;
+        m.p0 = cst(row_ptr)[atom];
+        m.p1 = cst(row_ptr)[atom + 1];
+#pragma unroll
+        for (int s = 0; s < SLOTS_HELD; ++s) m.word[s] = cst(lnb)[(long)lc * deg_max + s];
     };
-    // the next row's atom, layer word, slot list and pair range are fetched while
-    // the current row computes, which takes their dependent loads off the
-    // critical path
+    struct Onsite { double e[NO]; };
+    auto onsite = [&](int atom, Onsite &o) {
+#pragma unroll
+        for (int a = 0; a < NO; ++a) o.e[a] = cst(H_on)[(long)atom * NO + a];
+    };
+    auto valid = [&](int info) {
+        const int L = info & 255, n1 = (info >> 8) & 255, n2 = (info >> 16) & 255, n3 = (info >> 24) & 255;
+        return last ? n3 : (k - 1 >= L + 1 ? n3 : (k - 1 == L ? n2 : n1));
+    };
+    // a row's loads in flight: its own y'_j (X^(k-1)), r_(j-1) and r_(j-2) (zero
+    // outside their supports) and the first NS neighbours with their blocks
+    u32x4_t hrow{};
+    T xs[NO], r1[LANCZOS ? NO : 1], r2[LANCZOS ? NO : 1], x[NS][NO], h[NS][NR];
+    auto gather = [&](int s, int word, int p0) {
+        XR::template load<0>(XR::row_rsrc(Xp + (long)(word >> 8) * stride_row, true), lane, x[s]);
+        if constexpr (HL) return;
+        const auto hb = __builtin_amdgcn_make_buffer_rsrc((void *)(H + (long)(p0 + (word & 255)) * NB), 0,
+                                                          NB * (int)sizeof(T), 0x00027000);
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            h[s][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(hb, hoff[i], 0, 0));
+        }
+    };
+    auto fetch = [&](int l, const Rec &m) {
+        const int L = m.info & 255, nval = valid(m.info);
+        if constexpr (HL)
+            hrow = __builtin_amdgcn_raw_buffer_load_b128(
+                __builtin_amdgcn_make_buffer_rsrc((void *)(H + (long)m.p0 * NB), 0, (m.p1 - m.p0) * NB * (int)sizeof(T), 0x00027000),
+                lane * 16, 0, 0);
+        XR::template load<0>(XR::row_rsrc(Xp + (long)l * stride_row, L <= k - 1), lane, xs);
+        if constexpr (LANCZOS) {
+            XR::template load<AUX_NT>(XR::row_rsrc(Rb + (long)l * stride_row, L <= k - 2), lane, r1);
+            XR::template load<AUX_NT>(XR::row_rsrc(Ra + (long)l * stride_row, L <= k - 3), lane, r2);
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (s < nval) gather(s, m.word[s], m.p0);
+    };
+    // slot s's block: in its registers, or (HL) read from the wave's LDS slice
+    auto add = [&](Acc<NO> &sum, int s, int word) {
+        if constexpr (HL) {
+#pragma unroll
+            for (int i = 0; i < NR; ++i) h[s][i] = s_h[w][(word & 255) * NB + hoff[i] / 4];
+        }
+        Block<NO>::mul(h[s], x[s], sum.q, sum.tail);
+    };
     int l = chunk * NW + w;
-    int g_n = 0, info_n = 0, slots_n = 0, p0_n = 0, p1_n = 0, tm_n = -1;
+    Rec m, mn;
+    Onsite on;
+    int atom_n = 0;
     if (l < nrow) {
-        g_n = cst(sup)[l];
-        info_n = cst(rinfo)[l];
-        if constexpr (TR) tm_n = cst(rmask)[l];
-        slots_n = lane < deg_max ? lnb[(long)l * deg_max + lane] : 0;
-        p0_n = cst(row_ptr)[g_n];
-        p1_n = cst(row_ptr)[g_n + 1];
-        if constexpr (!HS) h_copy((const float *)(H + (long)p0_n * NB), (float *)sH, (p1_n - p0_n) * NB);
+        record(l, atom_of(l), m);
+        atom_n = atom_of(l + RS);
+        fetch(l, m);
+        onsite(m.atom, on);
+        // stores that go nowhere: the waits in the loop count the operations behind
+        // the ones they wait for, and the first row is to have as many as the others
+        const S none[NO] = {};
+        XR::store(XR::row_rsrc(Xc, false), lane, none);
+        if constexpr (LANCZOS) XR::store(XR::row_rsrc(Xc, false), lane, none);
     }
     for (; l < nrow; l += RS) {
-        const int g = g_n, info = info_n, slots_all = slots_n, p0 = p0_n, deg = p1_n - p0_n, tm = tm_n;
-        if (l + RS < nrow) {
-            g_n = cst(sup)[l + RS];
-            info_n = cst(rinfo)[l + RS];
-            if constexpr (TR) tm_n = cst(rmask)[l + RS];
-            slots_n = lane < deg_max ? lnb[(long)(l + RS) * deg_max + lane] : 0;
-            p0_n = cst(row_ptr)[g_n];
-            p1_n = cst(row_ptr)[g_n + 1];
+        const bool more = l + RS < nrow;
+        const int L = m.info & 255, nval = valid(m.info);
+        T acc[NO];
+#pragma unroll
+        for (int a = 0; a < NO; ++a) acc[a] = (float)on.e[a] * xs[a];
+        if constexpr (HL) *(f32x4_t *)&s_h[w][4 * lane] = __builtin_bit_cast(f32x4_t, hrow);
+        record(l + RS, atom_n, mn);
+        atom_n = atom_of(l + 2 * RS);
+        Acc<NO> sum;
+        sum.start(acc);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (s < nval) add(sum, s, m.word[s]);
+        constexpr int NP = (SLOTS_HELD + NS - 1) / NS;
+        static_for<NP - 1>([&](auto p) {
+            constexpr int S0 = (decltype(p)::value + 1) * NS;
+            if (S0 < nval) {
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    if (S0 + s < SLOTS_HELD && S0 + s < nval) gather(s, m.word[S0 + s < SLOTS_HELD ? S0 + s : 0], m.p0);
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    if (S0 + s < SLOTS_HELD && S0 + s < nval) add(sum, s, m.word[S0 + s < SLOTS_HELD ? S0 + s : 0]);
+            }
+        });
+        for (int s0 = SLOTS_HELD; s0 < nval; s0 += NS) {
+            int word[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) word[s] = cst(lnb)[(long)l * deg_max + min(s0 + s, nval - 1)];
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (s0 + s < nval) gather(s, word[s], m.p0);
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (s0 + s < nval) add(sum, s, word[s]);
         }
-        const int L = info & 255, n1 = (info >> 8) & 255, n2 = (info >> 16) & 255, n3 = (info >> 24) & 255;
-        const bool has_prev = last || L <= k - 1;
-        const int nval = last ? n3 : (k - 1 >= L + 1 ? n3 : (k - 1 == L ? n2 : n1));
-        const int slots = (lane < nval) ? slots_all : 0;
-        // the row's H blocks (contiguous pairs p0 .. p0 + deg): in the LDS slice
-        // (copied there after the previous row), or (HS) read with scalar loads
-        // straight into SGPR operands from their wave-uniform addresses.  HS
-        // measured 11-34% faster for FP64 and slower for FP32; FP32 uses it only
-        // where the LDS slice would not fit a workgroup.
-        constexpr bool H_SCALAR = HS;
-        const T *hsrc = H + (long)p0 * NB;
-        (void)deg;
-        const S *xrow = Xp + (long)l * stride_row + lane;
-        T acc[NO], xs[NO], r1[LANCZOS ? NO : 1], r2[LANCZOS ? NO : 1];
-#pragma unroll
-        for (int a = 0; a < NO; ++a) {
-            xs[a] = has_prev ? (T)xrow[a * 64] : T(0);
-            acc[a] = from_f64<T>(cst(H_on)[(long)g * NO + a]) * xs[a];
-        }
-        // gather a group of G slots (slots past nval re-read this row, harmless,
-        // and are masked in the product)
-        auto gather = [&](int s0, T (&x)[G][NO], int (&hoff)[G]) {
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const int su = s0 + u < nval ? s0 + u : 0;
-                const int pk = __builtin_amdgcn_readlane(slots, su);
-                const S *xn = (s0 + u < nval) ? Xp + (long)(pk >> 8) * stride_row + lane : xrow;
-                hoff[u] = (pk & 255) * NB;
-#pragma unroll
-                for (int b = 0; b < NO; ++b) x[u][b] = (T)xn[b * 64];
-            }
-        };
-        auto product = [&](int s0, const T (&x)[G][NO], const int (&hoff)[G]) {
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                if (s0 + u < nval) {
-                    const T *h = H_SCALAR ? hsrc + hoff[u] : sH + hoff[u];
-#pragma unroll
-                    for (int a = 0; a < NO; ++a)
-#pragma unroll
-                        for (int b = 0; b < NO; ++b)
-                            acc[a] = fma(h[NO == 5 ? d_packed_index(a, b) : a * NO + b], x[u][b], acc[a]);
-                }
-            }
-        };
-        auto h_ready = [&]() {
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_s_waitcnt(0);      // the row's H blocks have reached LDS
-            __builtin_amdgcn_wave_barrier();
-        };
-        if constexpr (PIPE) {
-            T xa[G][NO], xb[G][NO];
-            int ha[G], hb[G];
-            if (nval > 0) {
-                gather(0, xa, ha);
-                h_ready();
-            }
-            for (int s0 = 0; s0 < nval; s0 += 2 * G) {
-                if (s0 + G < nval) gather(s0 + G, xb, hb);
-                product(s0, xa, ha);
-                if (s0 + G < nval) {
-                    if (s0 + 2 * G < nval) gather(s0 + 2 * G, xa, ha);
-                    product(s0 + G, xb, hb);
-                }
-            }
-        } else {
-            for (int s0 = 0; s0 < nval; s0 += G) {
-                T x[G][NO];
-                int hoff[G];
-                gather(s0, x, hoff);
-                if (s0 == 0) h_ready();
-                product(s0, x, hoff);
-            }
-        }
+        sum.get(acc);
         // path radius: a column keeps the row only within r_max of its atom
         if constexpr (TR) {
-            if (!((tm >> (lane / NO)) & 1)) {
+            if (!((m.mask >> (lane / NO)) & 1)) {
 #pragma unroll
                 for (int a = 0; a < NO; ++a) acc[a] = T(0);
             }
         }
-        (void)tm;
-        __builtin_amdgcn_wave_barrier();   // all lanes done with sH before the next row's copy
-        if constexpr (!HS) {
-            if (nval == 0) __builtin_amdgcn_s_waitcnt(0);   // this row's copy (unused) has landed
-            if (l + RS < nrow) h_copy((const float *)(H + (long)p0_n * NB), (float *)sH, (p1_n - p0_n) * NB);
-        }
-        S *xo = Xc + (long)l * stride_row + lane;
+        S rw[NO], yw[NO];
         if constexpr (LANCZOS) {
-            // the row's own r_(j-1) and r_(j-2) (zero outside their supports),
-            // loaded after the products so that they hold no registers there;
-            // read once, so non-temporal loads keep them from displacing the
-            // gathered rows in L2 (1% on the FP32 pass)
-            const bool h1 = L <= k - 2, h2 = L <= k - 3;
-            const long off = (long)l * stride_row + lane;
-#pragma unroll
-            for (int a = 0; a < NO; ++a) {
-                r1[a] = h1 ? (T)__builtin_nontemporal_load(&Rb[off + a * 64]) : T(0);
-                r2[a] = h2 ? (T)__builtin_nontemporal_load(&Ra[off + a * 64]) : T(0);
-            }
-            S *ro = Ra + (long)l * stride_row + lane;
 #pragma unroll
             for (int a = 0; a < NO; ++a) {
                 const T hrp = (xs[a] + lbp * r2[a]) * linv;      // H r_(j-1) at this row
                 const T hr = acc[a] - lcj * hrp;                 // H r_j
                 const S rj = (S)(xs[a] - lcj * r1[a]);           // r_j
                 const S y = (S)(ls * hr - lbeta * r1[a]);        // y'_(j+1)
-                // r_j is zero on the newest layer (L = k, where y'_j and r_(j-1)
-                // are) and no later pass reads it there: stored on the older
-                // layers only
-                if (keep) {
-                    if (has_prev) __builtin_nontemporal_store(rj, &ro[a * 64]);
-                    __builtin_nontemporal_store(y, &xo[a * 64]);
-                }
+                rw[a] = rj;
+                yw[a] = y;
                 // sums of the vectors as stored
                 const double rd = (double)(T)rj, yd = (double)(T)y;
                 so = fma(rd, yd, so);
@@ -909,16 +1269,35 @@ k_step(Batch bt, int k, int K, int last, int keep, int fin, int nch, int chunk_r
                 sx = fma(rd, rd, sx);
             }
         } else {
-            if (keep) {
-#pragma unroll
-                for (int a = 0; a < NO; ++a) __builtin_nontemporal_store((S)acc[a], &xo[a * 64]);
-            }
 #pragma unroll
             for (int a = 0; a < NO; ++a) {
+                yw[a] = (S)acc[a];
                 so = fma((double)xs[a], (double)acc[a], so);
                 se = fma((double)acc[a], (double)acc[a], se);
             }
         }
+        // The next row's loads go out before this row's stores: vector memory
+        // operations complete in order, and a load behind the stores would wait
+        // for their way to memory.
+        // The pins keep the sums above on this side of the loads: moved behind them
+        // they would hold the row's own vectors, and the new ones would need copies,
+        // which wait for them.
+#pragma unroll
+        for (int a = 0; a < NO; ++a) {
+            pin(yw[a]);
+            if constexpr (LANCZOS) pin(rw[a]);
+        }
+        pin(so);
+        pin(se);
+        if constexpr (LANCZOS) pin(sx);
+        if (more) fetch(l + RS, mn);
+        onsite(mn.atom, on);
+        m = mn;
+        // r_j is zero on the newest layer (L = k, where y'_j and r_(j-1) are) and
+        // no later pass reads it there: stored on the older layers only
+        XR::store(XR::row_rsrc(Xc + (long)l * stride_row, keep), lane, yw);
+        if constexpr (LANCZOS)
+            XR::store(XR::row_rsrc(Ra + (long)l * stride_row, keep && L <= k - 1), lane, rw);
     }
     s_red[0][w][lane] = so;
     s_red[1][w][lane] = se;
@@ -996,7 +1375,6 @@ __global__ void k_reduce(Batch bt, int K, int n_max, StepParts sp, int chunk_row
 // FP32 accumulator; moments use the FP32 values of X^k and the stored BF16
 // X^(k-1); X^k is rounded to BF16 (nearest even) when stored.
 typedef short bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ inline float bf16_to_f32(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 __device__ inline unsigned short f32_to_bf16(float f)
@@ -1204,7 +1582,6 @@ typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 __device__ inline s16x4_t words_to_s16x4(unsigned lo, unsigned hi)
 {
-    typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(s16x4_t, (u32x2_t){lo, hi});
 }
 // the two 16-bit formats of the packed rows: halves of a word to FP32, two
@@ -1506,17 +1883,6 @@ k_lstep16(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, i
     }
 }
 
-// dynamic LDS of a step launch that stages the rows' H blocks (one slice of
-// deg_max blocks per wavefront)
-static inline size_t h_lds_bytes(const bop_plan &p, int wgt, size_t elem)
-{
-    return (size_t)(wgt / 64) * h_slice(p.deg_max, p.n_orb == 5 ? BOP_D_PACKED : p.n_orb * p.n_orb) * elem;
-}
-
-// static LDS of k_step (its per-wave partial sums), which the H slices share
-// the workgroup's LDS with
-static inline size_t step_static_lds(int wgt, int lanczos) { return (size_t)(lanczos ? 3 : 2) * wgt * 8; }
-
 template <int NO>
 int run_moments_bf16(const bop_plan &p, const int *row_ptr, const double *H_on, const void *Hv, double *mu,
                      char *ws, const Layout &lay, hipStream_t st)
@@ -1575,7 +1941,6 @@ int run_moments(const bop_plan &p, const int *row_ptr, const double *H_on, const
     char *xb = ws + lay.x;
     double *part = (double *)(ws + lay.part);
     const StepParts sp = step_parts(p);
-    const size_t lds_max = (size_t)device_lds_per_block();
     for (int first = 0; first < p.n_tiles; first += p.batch_tiles) {
         Batch bt{first, min(p.batch_tiles, p.n_tiles - first)};
         k_x0<T, NO><<<bt.count, 256, 0, st>>>(bt, p.n_max, p.tile_atoms, sizes, tiles, lay.tile_stride, xb,
@@ -1592,18 +1957,14 @@ int run_moments(const bop_plan &p, const int *row_ptr, const double *H_on, const
             if (nch <= 0) continue;
             dim3 grid((unsigned)(nb8 * nch * 8));
 #define BOP_STEP_ARGS                                                                                 \
-    bt, k, K, last, keep, 0, nch, p.chunk_rows, p.deg_max, p.rows_cap, row_ptr, H_on, H, sizes, tiles,  \
+    bt, k, K, last, keep, nch, p.chunk_rows, p.deg_max, p.rows_cap, row_ptr, H_on, H, sizes, tiles,     \
         lay.tile_stride, xb, lay.x_stride, part + sp.off[k], nullptr
-#define BOP_STEP_TR(W, TR)                                                                            \
-    do {                                                                                              \
-        const size_t lds = h_lds_bytes(p, W, sizeof(T));                                              \
-        if constexpr (sizeof(T) == 8) {                                                               \
-            k_step<T, NO, W, 0, T, true, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS);                      \
-        } else {                                                                                      \
-            if (lds + step_static_lds(W, 0) > lds_max)                                                \
-                k_step<T, NO, W, 0, T, true, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS);                  \
-            else k_step<T, NO, W, 0, T, false, TR><<<grid, W, lds, st>>>(BOP_STEP_ARGS);              \
-        }                                                                                             \
+#define BOP_STEP_TR(W, TR) \
+    do { \
+        if constexpr (sizeof(T) == 8) k_step<NO, W, 0, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
+        else if (NO == 5 && p.deg_max <= HL_PAIRS) \
+            k_step32<NO, W, 0, T, NO == 5, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
+        else k_step32<NO, W, 0, T, false, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
     } while (0)
 #define BOP_STEP(W)                                                                                   \
     do {                                                                                              \
@@ -1697,7 +2058,7 @@ __global__ void k_l0(Batch bt, int n_max, const int *__restrict__ sizes_, const 
         S *X0 = (S *)(xbase + x_stride * ((size_t)nbuf * t));
         for (int e = threadIdx.x; e < Bt * NO * 64; e += blockDim.x) {
             int l = e / (NO * 64), rest = e % (NO * 64), al = rest / 64, c = rest % 64;
-            X0[(long)l * NO * 64 + al * 64 + c] = (c == l * NO + al) ? S(1) : S(0);
+            X0[(long)l * NO * 64 + XRow<S, NO>::at(al, c)] = (c == l * NO + al) ? S(1) : S(0);
         }
     }
 }
@@ -2024,7 +2385,6 @@ int run_lanczos(const bop_plan &p, const int *row_ptr, const double *H_on, const
     const char *tiles = ws + lay.tiles;
     char *xb = ws + lay.x;
     double *part = (double *)(ws + lay.part);
-    const size_t lds_max = (size_t)device_lds_per_block();
     double *lc = (double *)(ws + lay.lc);
     // breakdown threshold on b^2 relative to b_1^2, above the rounding level of the stored vectors
     const double thr = p.dtype == BOP_F64 ? 1e-14 : (p.dtype == BOP_F32 ? 1e-10 : 1e-7);
@@ -2044,18 +2404,14 @@ int run_lanczos(const bop_plan &p, const int *row_ptr, const double *H_on, const
             const int keep = k < steps;
             dim3 grid((unsigned)(nb8 * nch * 8));
 #define BOP_LSTEP_ARGS                                                                                \
-    bt, k, K, last, keep, 0, nch, p.chunk_rows, p.deg_max, p.rows_cap, row_ptr, H_on, (const T *)Hv,    \
+    bt, k, K, last, keep, nch, p.chunk_rows, p.deg_max, p.rows_cap, row_ptr, H_on, (const T *)Hv,       \
         sizes, tiles, lay.tile_stride, xb, lay.x_stride, part, lc
-#define BOP_LSTEP_TR(W, TR)                                                                           \
-    do {                                                                                              \
-        const size_t lds = h_lds_bytes(p, W, sizeof(T));                                              \
-        if constexpr (sizeof(T) == 8) {                                                               \
-            k_step<T, NO, W, 1, S, true, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS);                     \
-        } else {                                                                                      \
-            if (lds + step_static_lds(W, 1) > lds_max)                                                \
-                k_step<T, NO, W, 1, S, true, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS);                 \
-            else k_step<T, NO, W, 1, S, false, TR><<<grid, W, lds, st>>>(BOP_LSTEP_ARGS);             \
-        }                                                                                             \
+#define BOP_LSTEP_TR(W, TR) \
+    do { \
+        if constexpr (sizeof(T) == 8) k_step<NO, W, 1, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
+        else if (NO == 5 && p.deg_max <= HL_PAIRS) \
+            k_step32<NO, W, 1, S, NO == 5, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
+        else k_step32<NO, W, 1, S, false, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
     } while (0)
 #define BOP_LSTEP(W)                                                                                  \
     do {                                                                                              \

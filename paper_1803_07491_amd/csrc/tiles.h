@@ -28,7 +28,7 @@ __device__ inline int tile_chunks(int nrow, int chunk_rows, int nw)
 // workspace layout
 // ---------------------------------------------------------------------------
 // Bytes of one row of X (all 64 columns): n_orb values per column in
-// FP64/FP32 ([n_orb][64] per row), or n_orb padded to the MFMA slot width in
+// FP64/FP32 (planes of 16 bytes per column and one of the last orbital), or n_orb padded to the MFMA slot width in
 // BF16 ([64][slot width] per row).
 __host__ __device__ inline size_t x_row_bytes(int dtype, int n_orb)
 {
