@@ -31,7 +31,7 @@
 //    lane per column) from the gathered G^(k+1) of its neighbours and, with
 //    the same gathers and the row's own X^k, the per-pair contraction
 //    sum_(a,b) X^k[i a] G^(k+1)[j b] dH_(ij,ab)/dd, summed over the 64 columns
-//    by a wave reduction.  A pair's partial sums live in a per-tile slot
+//    through LDS.  A pair's partial sums live in a per-tile slot
 //    array from the row's first backward pass (k = n - L) to its last
 //    (k = L), where they are added to the pair's gradient with one FP64
 //    atomic per component.  Per column the sum is symmetric and the block
@@ -502,9 +502,8 @@ struct FBatch {
     int first, count;
 };
 
-// H and the derivative blocks are read at wave-uniform addresses through the
-// constant address space, so that their loads stay scalar loads also where the
-// kernel issues LDS-DMA loads (which the compiler takes as possible writes)
+// H blocks are read at wave-uniform addresses through the constant address
+// space, so that their loads are scalar loads
 template <typename T> using CT = const __attribute__((address_space(4))) T;
 
 // row offset of X^l in a tile's level store
@@ -547,8 +546,9 @@ __global__ void k_finit(FBatch bt, int n, const double *__restrict__ w, const in
     for (int e = threadIdx.x; e < Bt * SR; e += blockDim.x) {
         const int l = e / SR, rest = e % SR, a = rest / 64, c = rest % 64;
         const bool own = c == l * NO + a;
-        X0[e] = own ? T(1) : T(0);
-        Gn[e] = own ? (T)w[((long)sup[l] * NO + a) * (n + 1) + n] : T(0);
+        const int at = l * SR + XRow<T, NO>::at(a, c);
+        X0[at] = own ? T(1) : T(0);
+        Gn[at] = own ? (T)w[((long)sup[l] * NO + a) * (n + 1) + n] : T(0);
     }
 }
 
@@ -557,16 +557,34 @@ __global__ void k_finit(FBatch bt, int n, const double *__restrict__ w, const in
 // pass over a batch of tiles.  Launch numbering as in the moment passes: all
 // chunks of a tile on one XCD, rows dealt to the chunks in wave-sized groups.
 // A row's neighbour slots go in groups of GS: the group's rows of the operand
-// are gathered before any is used.  In the backward pass each lane's three
-// contraction values per slot go to the wave's LDS block [3 GS][65] and are
-// summed over the 64 columns by eight lanes per value, each adding every
-// eighth column, then three exchanges among the eight (a shuffle tree per
-// value, or a few lanes adding 32 columns each, cost more instructions).
+// are gathered before any is used.
+//
+// The backward pass is bound by its FP64 instructions and the waits between them
+// (a contracted slot costs 25 fused multiply-adds for G, 25 products and 45 more
+// for the three components, at five waves per SIMD), not by memory, so what is
+// not arithmetic on a lane's own column is kept off its path:
+//  * the slots to contract are one bit mask per row, from one load of the reverse
+//    pairs a row ahead;
+//  * a derivative block comes with the slot's gathers as three vector loads (its 16
+//    packed values in each 16-lane row) and reaches the products as a broadcasting
+//    operand; as 45 scalar operands it cost the wave a wait per slot and register
+//    spills;
+//  * each lane's three values per contracted slot go to the wave's LDS block and
+//    are summed over the columns for two such slots at once, by eight lanes per
+//    value, each adding every eighth column, then three exchanges among the eight (a
+//    shuffle tree per value, or a few lanes adding 32 columns each, cost more);
+//  * a row's running sums are read once before its slots and written once after
+//    them, all slots of a component side by side.
+// 11,664 atoms, n_max = 18, all passes: 203 -> 150 ms in FP64, 136 -> 101 in FP32;
+// 432 atoms: 2.72 -> 2.03 ms (before: the reverse pairs and running sums fetched per
+// group of slots where needed, both directions' slots reduced, derivative blocks as
+// scalars, an orbital per load).  Four waves per SIMD (fewer spills) is 1 % slower,
+// six 13 %; three slots per group 3 %.
 constexpr int GS = 2;                         // slots per gather group
 constexpr int TSTRIDE = 65;                   // LDS row of one value (64 columns + pad)
 
 template <typename T, int NO, bool BWD>
-__global__ void __launch_bounds__(FW)
+__global__ void __launch_bounds__(FW) __attribute__((amdgpu_waves_per_eu(BWD ? 5 : 8)))
 k_fstep(FBatch bt, int lev, int n, int K, int nch, int chunk_rows, int deg_max, int rows_cap,
         const int *__restrict__ row_ptr, const double *__restrict__ H_on, const T *__restrict__ H,
         const double *__restrict__ dH, const double *__restrict__ w, const int *__restrict__ rev,
@@ -576,8 +594,9 @@ k_fstep(FBatch bt, int lev, int n, int K, int nch, int chunk_rows, int deg_max, 
 {
     constexpr int NB = BOP_D_PACKED;
     constexpr int SR = NO * 64;
-    __shared__ double s_t[BWD ? NWF : 1][BWD ? 3 * GS * TSTRIDE : 1];
-    __shared__ unsigned s_sink[sizeof(T) == 4 ? NWF : 1][64];   // LDS copies of the L2 touches, never read
+    using XR = XRow<T, NO>;
+    __shared__ double s_t[BWD ? NWF : 1][BWD ? 6 * TSTRIDE : 1];   // two slots' values, or NO onsite ones
+    __shared__ double s_pair[BWD ? NWF : 1][BWD ? 3 * 64 : 1];   // a row's pair sums of this pass
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
     const int t = (q / nch) * 8 + xcd, chunk = q % nch;
     if (t >= bt.count) return;
@@ -608,39 +627,42 @@ k_fstep(FBatch bt, int lev, int n, int K, int nch, int chunk_rows, int deg_max, 
     if (BWD && lev >= 1 && lane < Bt * NO) wl = (T)w[((long)sup[lane / NO] * NO + lane % NO) * (n + 1) + lev];
     // reduction lanes: value vg of the group, columns sg, sg + 8, ..., sg + 56
     const int vg = lane >> 3, sg = lane & 7;
-    // the next row's atom, layer word, slot list and first pair are fetched
-    // while the current row computes
+    // the next row's atom, layer word, slot list, first pair, its pairs' reverses
+    // (one per lane) are fetched while the current row computes
     int l = chunk * NWF + wv;
-    int g_n = 0, info_n = 0, slots_n = 0, p0_n = 0;
+    int g_n = 0, info_n = 0, slots_n = 0, p0_n = 0, rev_n = 0;
     if (l < nrow) {
         g_n = __builtin_amdgcn_readfirstlane(sup[l]);
         info_n = __builtin_amdgcn_readfirstlane(rinfo[l]);
         slots_n = lane < deg_max ? lnb[(long)l * deg_max + lane] : 0;
         p0_n = __builtin_amdgcn_readfirstlane(row_ptr[g_n]);
+        if (BWD) rev_n = lane < (info_n >> 24 & 255) ? rev[(long)p0_n + (slots_n & 255)] : -1;
     }
     for (; l < nrow; l += RS) {
         const int g = g_n, info = info_n, slots = slots_n, p0 = p0_n;
+        // the pairs contracted here: the directions of lower index (g_reverse(p) =
+        // -g_p), one bit per slot
+        const unsigned long long canon = BWD ? __ballot(rev_n > p0 + (slots & 255)) : 0ull;
         if (l + RS < nrow) {
             g_n = __builtin_amdgcn_readfirstlane(sup[l + RS]);
             info_n = __builtin_amdgcn_readfirstlane(rinfo[l + RS]);
             slots_n = lane < deg_max ? lnb[(long)(l + RS) * deg_max + lane] : 0;
             p0_n = __builtin_amdgcn_readfirstlane(row_ptr[g_n]);
+            if (BWD) rev_n = lane < (info_n >> 24 & 255) ? rev[(long)p0_n + (slots_n & 255)] : -1;
         }
         const int L = info & 255, n1 = (info >> 8) & 255, n2 = (info >> 16) & 255, n3 = (info >> 24) & 255;
         const int nval = Lp >= L + 1 ? n3 : (Lp == L ? n2 : n1);
-        const int *lrow = lnb + (long)l * deg_max;
         const bool has_prev = L <= Lp;
-        T acc[NO], xk[NO], xs[NO];
+        T acc[NO], xk[NO] = {}, xs[NO] = {};
+        if (has_prev) XR::template load<false>(src + (size_t)l * SR, lane, xs);
+        if (BWD) XR::template load<false>(Xk + (size_t)l * SR, lane, xk);
 #pragma unroll
-        for (int a = 0; a < NO; ++a) {
-            xs[a] = has_prev ? src[(size_t)l * SR + a * 64 + lane] : T(0);
-            acc[a] = (T)H_on[(long)g * NO + a] * xs[a];
-            xk[a] = BWD ? Xk[(size_t)l * SR + a * 64 + lane] : T(0);
-        }
+        for (int a = 0; a < NO; ++a) acc[a] = (T)H_on[(long)g * NO + a] * xs[a];
         // a row's pair sums run from its first backward pass (lev = n - L, at
         // most n - 1) to its last (lev = L)
         const bool first = BWD && lev == min(n - L, n - 1), last = BWD && lev == L;
         double *acc_row = acc_t + (size_t)l * deg_max * 3;
+        const double run = BWD && lane < 3 * n3 ? acc_row[lane] : 0.0;      // used once the slots are done
         if (BWD && theta_on) {
             // onsite elements Theta~_(ia,ia): X^lev[i a] G^(lev+1)[i a] summed
             // over the columns, kept like the pair sums from the row's first
@@ -669,29 +691,40 @@ k_fstep(FBatch bt, int lev, int n, int K, int nch, int chunk_rows, int deg_max, 
             }
             __builtin_amdgcn_wave_barrier();
         }
-        for (int s0 = 0; s0 < nval; s0 += GS) {
-            if (sizeof(T) == 4) {
-                // FP32 vectors: the next group's H blocks (and derivative
-                // blocks) are fetched into L2 by an LDS-DMA load whose LDS copy
-                // is never read, so that their scalar loads find them there
-                // (with FP64 vectors this costs the backward pass an occupancy
-                // step and gains nothing)
-                const int u = lane >> 2, part = lane & 3;
-                const int sn = s0 + GS + u;
-                const int sw = __shfl(slots, sn < 64 ? sn : 0);
-                if (u < GS && sn < nval && (BWD || part == 0)) {
-                    const long pn = (long)p0 + (sw & 255);
-                    const void *a = part == 0 ? (const void *)(H + pn * NB) : (const void *)(dH + (pn * 3 + part - 1) * NB);
-                    __builtin_amdgcn_global_load_lds(a, (__attribute__((address_space(3))) void *)&s_sink[wv][0], 4, 0, 0);
-                }
+        // column sums of the contracted slots held in the wave's LDS block (nc of
+        // them, the latest slot s1, the one before it sp) into the row's pair sums
+        double *sp_row = &s_pair[BWD ? wv : 0][0];
+        int nc = 0, s_a = 0, s_b = 0;
+        auto column_sums = [&]() {
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_s_waitcnt(0xc07f);        // the block's LDS writes are done
+            __builtin_amdgcn_wave_barrier();
+            double v = 0.0;
+            if (vg < 3 * nc) {
+                const double *row = st + vg * TSTRIDE + sg;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) v += row[8 * c];
             }
+            v += __shfl_xor(v, 1);
+            v += __shfl_xor(v, 2);
+            v += __shfl_xor(v, 4);
+            if (sg == 0 && vg < 3 * nc) sp_row[3 * (vg < 3 ? s_a : s_b) + vg % 3] = v;
+            __builtin_amdgcn_wave_barrier();
+            nc = 0;
+        };
+        for (int s0 = 0; s0 < nval; s0 += GS) {
             T xn[GS][NO];
+            double dh[GS][3] = {};
 #pragma unroll
             for (int u = 0; u < GS; ++u) {
                 const int su = s0 + u < nval ? s0 + u : s0;
                 const int jl = __builtin_amdgcn_readlane(slots, su) >> 8;
+                XR::template load<false>(src + (size_t)jl * SR, lane, xn[u]);
+                if (BWD && s0 + u < nval && (canon >> (s0 + u) & 1)) {
+                    const double *d = dH + ((long)p0 + (__builtin_amdgcn_readlane(slots, s0 + u) & 255)) * 3 * NB;
 #pragma unroll
-                for (int b = 0; b < NO; ++b) xn[u][b] = src[(size_t)jl * SR + b * 64 + lane];
+                    for (int x = 0; x < 3; ++x) dh[u][x] = d[x * NB + (lane & 15)];
+                }
             }
             asm volatile("" ::: "memory");    // keep the group's gathers ahead of their uses
 #pragma unroll
@@ -703,70 +736,50 @@ k_fstep(FBatch bt, int lev, int n, int K, int nch, int chunk_rows, int deg_max, 
                 for (int a = 0; a < NO; ++a)
 #pragma unroll
                     for (int b = 0; b < NO; ++b) acc[a] = fma(h[d_packed_index(a, b)], xn[u][b], acc[a]);
-                // the contraction of the pair's canonical direction only (the
-                // one of lower index): g_reverse(p) = -g_p
-                if (BWD && __builtin_amdgcn_readfirstlane(rev[pp]) > pp) {
-                    const CT<double> *dh = (const CT<double> *)(dH + pp * 3 * NB);
+                if (BWD && (canon >> (s0 + u) & 1)) {
                     double t0 = 0.0, t1 = 0.0, t2 = 0.0;
-#pragma unroll
-                    for (int a = 0; a < NO; ++a)
-#pragma unroll
-                        for (int b = a; b < NO; ++b) {
-                            const double sab = a == b ? (double)xk[a] * (double)xn[u][a]
-                                                      : (double)xk[a] * (double)xn[u][b] + (double)xk[b] * (double)xn[u][a];
-                            const int e = d_packed_index(a, b);
-                            t0 = fma(sab, dh[e], t0);
-                            t1 = fma(sab, dh[NB + e], t1);
-                            t2 = fma(sab, dh[2 * NB + e], t2);
-                        }
-                    st[(3 * u) * TSTRIDE + lane] = t0;
-                    st[(3 * u + 1) * TSTRIDE + lane] = t1;
-                    st[(3 * u + 2) * TSTRIDE + lane] = t2;
-                } else if (BWD) {
-                    st[(3 * u) * TSTRIDE + lane] = 0.0;
-                    st[(3 * u + 1) * TSTRIDE + lane] = 0.0;
-                    st[(3 * u + 2) * TSTRIDE + lane] = 0.0;
+                    dpp_guard(dh[u][0]);
+                    dpp_guard(dh[u][1]);
+                    dpp_guard(dh[u][2]);
+                    static_for<NO>([&](auto ia) {
+                        static_for<NO>([&](auto ib) {
+                            constexpr int a = decltype(ia)::value, b = decltype(ib)::value;
+                            if constexpr (a <= b) {
+                                const double sab = a == b ? (double)xk[a] * (double)xn[u][a]
+                                                          : (double)xk[a] * (double)xn[u][b] + (double)xk[b] * (double)xn[u][a];
+                                constexpr int e = d_packed_index(a, b);
+                                fma_bcast<e>(t0, dh[u][0], sab);
+                                fma_bcast<e>(t1, dh[u][1], sab);
+                                fma_bcast<e>(t2, dh[u][2], sab);
+                            }
+                        });
+                    });
+                    double *sv = st + 3 * nc * TSTRIDE + lane;
+                    sv[0] = t0;
+                    sv[TSTRIDE] = t1;
+                    sv[2 * TSTRIDE] = t2;
+                    (nc == 0 ? s_a : s_b) = s0 + u;
+                    if (++nc == 2) column_sums();
                 }
-            }
-            if (BWD) {
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_s_waitcnt(0xc07f);        // the group's LDS writes are done
-                __builtin_amdgcn_wave_barrier();
-                const int ng = 3 * min(GS, nval - s0);
-                double v = 0.0;
-                if (vg < ng) {
-                    const double *row = st + vg * TSTRIDE + sg;
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) v += row[8 * c];
-                }
-                v += __shfl_xor(v, 1);
-                v += __shfl_xor(v, 2);
-                v += __shfl_xor(v, 4);
-                if (sg == 0 && vg < ng) {
-                    const int s = s0 + vg / 3, x = vg % 3;
-                    const long pp = (long)p0 + (lrow[s] & 255);
-                    double *ap = acc_row + s * 3 + x;
-                    if (rev[pp] > pp) {
-                        if (first && last) unsafeAtomicAdd(&gpair[3 * pp + x], 2.0 * v);
-                        else if (first) *ap = v;
-                        else if (last) unsafeAtomicAdd(&gpair[3 * pp + x], 2.0 * (*ap + v));
-                        else *ap += v;
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
             }
         }
-        if (BWD && first != last) {
-            // slots whose operand is zero at this pass: start their sums at
-            // zero (first pass) or hand them on (last pass)
-            for (int e = lane; e < 3 * (n3 - nval); e += 64) {
-                const int s = nval + e / 3, x = e % 3;
-                const long pp = (long)p0 + (lrow[s] & 255);
-                double *ap = acc_row + s * 3 + x;
-                if (rev[pp] <= pp) continue;
-                if (first) *ap = 0.0;
-                else unsafeAtomicAdd(&gpair[3 * pp + x], 2.0 * *ap);
+        if (BWD) {
+            if (nc > 0) column_sums();
+            // every slot's running sum: started (first pass), continued or handed on
+            // to the pair (last pass); slots whose operand is zero at this pass add
+            // nothing
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            __builtin_amdgcn_wave_barrier();
+            for (int e0 = 0; e0 < 3 * n3; e0 += 64) {
+                const int e = e0 + lane, sl = e / 3;
+                const int word = __shfl(slots, sl < 64 ? sl : 0);
+                if (e >= 3 * n3 || !(canon >> sl & 1)) continue;
+                double v = sl < nval ? sp_row[e] : 0.0;
+                if (!first) v = (e0 == 0 ? run : acc_row[e]) + v;
+                if (last) unsafeAtomicAdd(&gpair[3 * ((long)p0 + (word & 255)) + e % 3], 2.0 * v);
+                else acc_row[e] = v;
             }
+            __builtin_amdgcn_wave_barrier();
         }
         if (BWD) {
             if (lev == 0) continue;          // G^0 is not needed
@@ -776,8 +789,7 @@ k_fstep(FBatch bt, int lev, int n, int K, int nch, int chunk_rows, int deg_max, 
                     if (lane == l * NO + a) acc[a] += wl;
             }
         }
-#pragma unroll
-        for (int a = 0; a < NO; ++a) __builtin_nontemporal_store(acc[a], &dst[(size_t)l * SR + a * 64 + lane]);
+        XR::store(dst + (size_t)l * SR, lane, acc);
     }
 }
 

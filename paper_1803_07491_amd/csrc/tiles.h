@@ -5,6 +5,7 @@
 // bop_moments workspace.
 #pragma once
 #include "bop_internal.h"
+#include <type_traits>
 
 namespace bop {
 
@@ -35,6 +36,113 @@ __host__ __device__ inline size_t x_row_bytes(int dtype, int n_orb)
     if (dtype == BOP_BF16) return 2ull * 64 * (n_orb <= 8 ? 8 : 16);
     return (dtype == BOP_F64 ? 8ull : (dtype == BOP_F16 ? 2ull : 4ull)) * n_orb * 64;
 }
+
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+constexpr int AUX_NT = 2;           // non-temporal bit of a buffer access
+
+// Layout of a row of X (64 columns, one per lane): the orbitals are grouped into
+// planes of V values per lane, so that a lane reads or writes its column's
+// values of a row with one wide access per plane (16 bytes for FP64 and FP32)
+// instead of one per orbital; the orbital left over has a plane of its own.
+template <typename S, int NO> struct XRow {
+    static constexpr int V = sizeof(S) >= 4 ? 16 / (int)sizeof(S) : NO - 1;
+    static constexpr int NP = NO / V, TAIL = NP * V * 64;
+    static_assert(NO - NP * V == 1, "one orbital is left over");
+    typedef S vec __attribute__((ext_vector_type(V)));
+    // element of orbital a, column c
+    static __host__ __device__ int at(int a, int c) { return a < NP * V ? (a / V) * V * 64 + c * V + a % V : TAIL + c; }
+    template <bool NT, typename T> static __device__ inline void load(const S *row, int lane, T (&x)[NO])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const vec *q = (const vec *)(row + p * V * 64) + lane;
+            const vec v = NT ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+            for (int e = 0; e < V; ++e) x[p * V + e] = (T)v[e];
+        }
+        const S *q = row + TAIL + lane;
+        x[NO - 1] = (T)(NT ? __builtin_nontemporal_load(q) : *q);
+    }
+    // non-temporal
+    static __device__ inline void store(S *row, int lane, const S (&x)[NO])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            vec v;
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = x[p * V + e];
+            __builtin_nontemporal_store(v, (vec *)(row + p * V * 64) + lane);
+        }
+        __builtin_nontemporal_store(x[NO - 1], row + TAIL + lane);
+    }
+    // The same through a buffer descriptor of the row: its base is wave-uniform, so
+    // that addresses cost no vector instruction, and one of no bytes (on false) reads
+    // zeros and drops stores without a branch, which would hide the number of
+    // accesses in flight from the waits that follow it.
+    static __device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const S *row, bool on)
+    {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, on ? NO * 64 * (int)sizeof(S) : 0, 0x00027000);
+    }
+    template <int AUX, typename T> static __device__ inline void load(__amdgpu_buffer_rsrc_t r, int lane, T (&x)[NO])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            vec v;
+            if constexpr (sizeof(vec) == 16)
+                v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + p * 1024, 0, AUX));
+            else v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(r, lane * 8 + p * 512, 0, AUX));
+#pragma unroll
+            for (int e = 0; e < V; ++e) x[p * V + e] = (T)v[e];
+        }
+        if constexpr (sizeof(S) == 8)
+            x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+        else if constexpr (sizeof(S) == 4)
+            x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+        else x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+    }
+    // non-temporal
+    static __device__ inline void store(__amdgpu_buffer_rsrc_t r, int lane, const S (&x)[NO])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            vec v;
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = x[p * V + e];
+            if constexpr (sizeof(vec) == 16)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, lane * 16 + p * 1024, 0, AUX_NT);
+            else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, lane * 8 + p * 512, 0, AUX_NT);
+        }
+        if constexpr (sizeof(S) == 8)
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
+        else if constexpr (sizeof(S) == 4)
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
+        else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
+    }
+};
+
+// compile-time loop: f(integral_constant<int, I>) for I = 0 .. N-1
+template <int N, int I = 0, typename F> __device__ inline void static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
+}
+
+// acc += (lane K of every 16-lane row of h) * x.  A broadcasting operand costs
+// no instruction of its own.  The operand may not be read within two waits of
+// a VALU write; callers pass h as loaded, with dpp_guard() before the first use.
+template <int K> __device__ inline void fma_bcast(float &acc, float h, float x)
+{
+    asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(h), "v"(x), "n"(K));
+}
+template <int K> __device__ inline void fma_bcast(double &acc, double h, double x)
+{
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(h), "v"(x), "n"(K));
+}
+template <typename T> __device__ inline void dpp_guard(T &h) { asm("s_nop 1" : "+v"(h)); }
 
 struct Layout {
     size_t sizes;       // int [n_tiles][MAXK + 2]: rows of U^k per tile; [0] = -1 marks a failed tile
