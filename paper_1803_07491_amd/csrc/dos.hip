@@ -5,7 +5,7 @@
 //    n_max by the chain recursion of App. B.4 with the constant terminator, and
 //    Jackson damping (Eq. Jackson);
 //  * electron counts, bond energies and DOS at E (App. B.2), the Fermi level
-//    by bisection (Sec. II), four halvings per pass over the coefficients,
+//    by bisection (Sec. II), four or eight halvings per pass over the coefficients,
 //    per-atom sums (App. A.1 Eq. TB-Ubond).
 //
 // The chain recursion is evaluated on the computed levels 0..L-1 plus one
@@ -260,6 +260,24 @@ k_recursion_reg(int n_rows, int n_max, const double *__restrict__ mu, int bw_mod
 // ---------------------------------------------------------------------------
 // expansion coefficients g_m sigma_m, m-major
 // ---------------------------------------------------------------------------
+// Jackson kernel of length n_exp adapted to U polynomials: g_m = g^J_(m+1)/g^J_1
+// (whole block)
+__device__ inline void jackson_table(int n_exp, double *s_g)
+{
+    const double w = M_PI / (n_exp + 1.0);
+    double sw, cw;
+    sincos(w, &sw, &cw);
+    const double cotw = cw / sw;
+    const double g1 = ((double)n_exp * cw + sw * cotw) / (n_exp + 1.0);
+    for (int m = threadIdx.x; m <= n_exp; m += blockDim.x) {
+        int mm = m + 1;
+        double sm, cm;
+        sincos(w * mm, &sm, &cm);
+        double gj = ((double)(n_exp - mm + 1) * cm + sm * cotw) / (n_exp + 1.0);
+        s_g[m] = gj / g1;
+    }
+}
+
 template <int LM>
 __global__ void __launch_bounds__(DT)
 k_dos_coeffs(int n_rows, int n_max, int n_exp, const double *__restrict__ mu,
@@ -283,17 +301,7 @@ k_dos_coeffs(int n_rows, int n_max, int n_exp, const double *__restrict__ mu,
             for (int l = 1; l <= n; ++l) s_c[n * M + l] = s_c[(n - 1) * M + l - 1] + (l <= n - 1 ? s_c[(n - 1) * M + l] : 0.0);
         }
     }
-    {
-        // Jackson kernel of length n_exp adapted to U polynomials: g_m = g^J_(m+1)/g^J_1
-        const double w = M_PI / (n_exp + 1.0);
-        const double cotw = cos(w) / sin(w);
-        const double g1 = ((double)n_exp * cos(w) + sin(w) * cotw) / (n_exp + 1.0);
-        for (int m = threadIdx.x; m <= n_exp; m += blockDim.x) {
-            int mm = m + 1;
-            double gj = ((double)(n_exp - mm + 1) * cos(w * mm) + sin(w * mm) * cotw) / (n_exp + 1.0);
-            s_g[m] = gj / g1;
-        }
-    }
+    jackson_table(n_exp, s_g);
     __syncthreads();
     int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n_rows) return;
@@ -363,6 +371,124 @@ k_dos_coeffs(int n_rows, int n_max, int n_exp, const double *__restrict__ mu,
         }
     }
     if (!(big <= 1e4)) flags[r] |= BOP_FLAG_DIVERGENT;
+}
+
+
+// value of the lane below / above in the row of 16 lanes, 0 at its ends; of its first lane
+__device__ inline double row_below(double v) { return __builtin_amdgcn_update_dpp(0.0, v, 0x111, 0xf, 0xf, true); }
+__device__ inline double row_above(double v) { return __builtin_amdgcn_update_dpp(0.0, v, 0x101, 0xf, 0xf, true); }
+__device__ inline double row_first(double v) { return __builtin_amdgcn_update_dpp(0.0, v, 0x150, 0xf, 0xf, true); }
+
+// The same with 16 lanes per row, lane k carrying the chain's level k: one step of
+// the chain is then seven operations and two exchanges between neighbouring lanes
+// instead of a dozen levels' operations one after the other, which is what a row takes
+// while the rows are too few to fill the chip.  The tables are built by a lane per
+// column.  The operations on every value, and their order, are those of k_dos_coeffs.
+// 200 terms: 640 rows 109 -> 16 us, 5120 rows 123 -> 26, 40,960 rows 170 -> 90; at
+// 138,240 rows 210 against 187, where a lane per row has the chip full: the line
+// (CL_ROWS) lies between.
+constexpr int CL = 16;                                       // lanes per row: up to 15 levels and the delay level
+constexpr int CR = DT / CL;                                  // rows per block
+constexpr int CL_NMAX = 20;
+constexpr long CL_ROWS = 98304;
+
+__global__ void __launch_bounds__(DT)
+k_dos_coeffs_lanes(int n_rows, int n_max, int n_exp, const double *__restrict__ mu,
+                   const double *__restrict__ a, const double *__restrict__ b,
+                   const double *__restrict__ a_inf, const double *__restrict__ b_inf,
+                   double *__restrict__ gs, int *__restrict__ flags)
+{
+    constexpr int MM = CL_NMAX + 1;
+    __shared__ double s_p[MM * MM], s_c[MM * MM];            // p_mn, binomials
+    __shared__ double s_g[1025];                              // Jackson g_m
+    __shared__ double s_m[CR][MM], s_mh[CR][MM];              // mu_n / mu_0, normalised moments
+    const int M = n_max + 1;
+    const int k = threadIdx.x & (CL - 1), row = threadIdx.x / CL;
+    const long r = (long)blockIdx.x * CR + row;
+    const bool live = r < n_rows;
+    const long rr = live ? r : n_rows - 1;
+    const double ai = a_inf[rr], bi = b_inf[rr];
+    const int na = n_a_of(n_max), nb = n_b_of(n_max);
+    const double ak = k < na ? a[rr * na + k] : 0.0, bk = k <= nb ? b[rr * (nb + 1) + k] : 0.0;
+    const double bk1 = k + 1 <= nb ? b[rr * (nb + 1) + k + 1] : 0.0;
+    if (mu) {
+        const double *mr = mu + rr * M;
+        const double m0 = mr[0];
+        for (int n = k; n < M; n += CL) s_m[row][n] = mr[n] / m0;
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        if (wave == 0) {                                      // column l = lane of Pascal's triangle
+            double c = lane == 0 ? 1.0 : 0.0;
+            for (int n = 0; n < M; ++n) {
+                if (lane < M) s_c[n * M + lane] = c;
+                const double below = __shfl_up(c, 1);
+                c += lane > 0 ? below : 0.0;
+            }
+        } else if (wave == 1) {                               // column n = lane of the U polynomials
+            double p0 = 0.0, p1 = lane == 0 ? 1.0 : 0.0;
+            for (int m = 0; m < M; ++m) {
+                if (lane < M) s_p[m * M + lane] = p1;
+                const double below = __shfl_up(p1, 1);
+                const double p2 = (lane > 0 ? 2.0 * below : 0.0) - p0;
+                p0 = p1;
+                p1 = p2;
+            }
+        }
+    }
+    jackson_table(n_exp, s_g);
+    __syncthreads();
+    const int n_mom = (mu && bi > 1e-6) ? n_max : 0;
+    double big = 0.0;
+    if (n_mom != 0) {
+        for (int n = k; n < M; n += CL) {
+            double s = 0.0, pa = 1.0;                         // pa = (-a_inf)^l
+            for (int l = 0; l <= n; ++l) {
+                s += s_c[n * M + l] * pa * s_m[row][n - l];
+                pa *= -ai;
+            }
+            s_mh[row][n] = s / pow(2.0 * bi, (double)n);
+        }
+    }
+    __syncthreads();
+    if (n_mom == 0) {
+        if (live && k == 0) gs[r] = s_g[0];
+    } else {
+        for (int m = k; m < M && m <= n_exp; m += CL) {
+            double s = 0.0;
+            for (int n = 0; n <= m; ++n) s += s_p[m * M + n] * s_mh[row][n];
+            if (live) gs[(long)m * n_rows + r] = s_g[m] * s;
+            big = fmax(big, fabs(s_g[m] * s));
+        }
+    }
+    if (n_exp > n_mom) {
+        const int L = na > nb ? na : nb;
+        const double ah = k < na ? (ak - ai) / (2.0 * bi) : 0.0;
+        const double bh = k == 0 || k > L ? 0.0 : (k <= nb ? bk / (2.0 * bi) : 0.5);
+        const double bh1 = k + 1 <= nb ? bk1 / (2.0 * bi) : 0.5;
+        double z0 = 0.0, z1 = k == 0 ? 1.0 : 0.0;
+        // sixteen steps at a time, lane t keeping level 0 of the t-th, so that the
+        // table reads and stores are not between the steps
+        for (int m = 1; m <= n_exp; m += CL) {
+            double top = 0.0;
+#pragma unroll
+            for (int t = 0; t < CL; ++t) {
+                const double x = bh * row_below(z1);
+                const double full = 2.0 * (ah * z1 + x + bh1 * row_above(z1)) - z0;
+                z0 = z1;
+                z1 = k < L ? full : x + x;                    // the delay level; 0 beyond it
+                const double first = row_first(z1);
+                top = k == t ? first : top;
+            }
+            const int mm = m + k;
+            if (mm > n_mom && mm <= n_exp) {
+                const double v = s_g[mm] * top;
+                if (live) gs[(long)mm * n_rows + r] = v;
+                big = fmax(big, fabs(v));
+            }
+        }
+    }
+    const bool bad = !(big <= 1e4);
+    const unsigned long long any = __ballot(bad) >> (threadIdx.x & 48) & 0xffff;
+    if (live && k == 0 && any) flags[r] |= BOP_FLAG_DIVERGENT;
 }
 
 // ---------------------------------------------------------------------------
@@ -443,37 +569,252 @@ k_bracket_pick(unsigned n_blocks, const double *__restrict__ part, FermiState *s
     }
 }
 
-// Fermi level by bisection (Sec. II), four halvings per pass: the pass
-// evaluates the electron count at the 15 midpoints the next four halvings can
-// visit (a binary tree whose nodes are formed exactly as sequential bisection
-// forms them, mid = (lo + hi)/2), reading each orbital's coefficients once;
-// a one-block launch then replays the four decisions.  The decisions, and
-// hence the root found when the count is not monotone, are those of plain
-// bisection.
-constexpr int FT_LEVELS = 4, FT_NODES = (1 << FT_LEVELS) - 1;
-constexpr int FT_MAX_HALVINGS = 64;                           // as many as plain bisection takes at most
-constexpr int FT_PASSES = (FT_MAX_HALVINGS + FT_LEVELS - 1) / FT_LEVELS;
-
-__device__ inline void tree_points(double lo, double hi, double *mid)
+// Fermi level by bisection (Sec. II), LEVELS halvings per pass: a pass evaluates
+// the electron count at the 2^LEVELS - 1 midpoints that its halvings can visit (a
+// binary tree in heap order whose nodes are formed exactly as sequential bisection
+// forms them, mid = (lo + hi)/2), and the decisions are then replayed.  They, and
+// hence the root found when the count is not monotone, are those of plain bisection.
+constexpr int FT_MAX_HALVINGS = 64;            // as many as plain bisection takes at most
+constexpr int FP_ROWS = 32;                    // rows per row block (one per lane of half a wave)
+constexpr int FP_GROUPS = DT / FP_ROWS;        // thread groups of a block, each with its own nodes
+constexpr int FP_RUN = 26;                     // coefficients a thread stages
+constexpr int FP_CH = 202;                     // terms held in LDS: what lets three blocks share a CU
+static_assert(FP_CH <= FP_GROUPS * FP_RUN && FP_CH > (FP_GROUPS - 1) * FP_RUN, "the last group stages what is left");
+constexpr int ft_nodes(int levels) { return (1 << levels) - 1; }
+// A pass's partials: where few rows take many nodes, the nodes of a row block side by
+// side; else the row blocks of a node (a multiple of four of them), as the sums read them.
+__host__ __device__ inline size_t ft_pitch(unsigned n_rb) { return (n_rb + 3) / 4 * 4; }
+template <int LEVELS> __device__ inline size_t ft_at(size_t pitch, unsigned rb, int p)
 {
-    // node i (1-based, heap order) covers [l_i, h_i]; children split at mid_i
-    double l[FT_NODES + 1], h[FT_NODES + 1];
-    l[1] = lo;
-    h[1] = hi;
-#pragma unroll
-    for (int i = 1; i <= FT_NODES; ++i) {
-        mid[i - 1] = 0.5 * (l[i] + h[i]);
-        if (2 * i + 1 <= FT_NODES) {
-            l[2 * i] = l[i]; h[2 * i] = mid[i - 1];
-            l[2 * i + 1] = mid[i - 1]; h[2 * i + 1] = h[i];
-        }
-    }
+    return LEVELS == 8 ? (size_t)rb * 256 + p : (size_t)p * pitch + rb;
 }
 
-// Two lanes share an orbital row: lane h of the pair takes nodes 8h .. 8h+7
-// (the last lane 7 nodes), which halves the registers per lane and doubles
-// the rows' loads in flight; both lanes read the same coefficients.
-constexpr int FT_HALF = (FT_NODES + 1) / 2;
+// midpoint of the tree's node `heap` (1-based) under [lo, hi]
+__device__ inline double tree_mid(double lo, double hi, int heap)
+{
+    double l = lo, h = hi;
+    for (int bit = 30 - __clz(heap); bit >= 0; --bit) {
+        const double m = 0.5 * (l + h);
+        if (heap >> bit & 1) l = m; else h = m;
+    }
+    return 0.5 * (l + h);
+}
+
+// The halvings of a pass over [st.lo, st.hi], tot[node] the count at its nodes
+// (count < n_elec: lo = mid, else hi = mid), stopping when a midpoint equals an end
+// of its bracket or after the most halvings plain bisection takes.
+__device__ inline FermiState tree_descend(FermiState st, int levels, double n_elec, const double *tot)
+{
+    double l = st.lo, h = st.hi;
+    int node = 1;
+    for (int lev = 0; lev < levels; ++lev) {
+        const double m = 0.5 * (l + h);
+        if (st.halvings >= FT_MAX_HALVINGS || m <= l || m >= h) { st.done = 1.0; break; }
+        if (2.0 * tot[node - 1] < n_elec) { l = m; node = 2 * node + 1; }
+        else { h = m; node = 2 * node; }
+        st.halvings += 1.0;
+    }
+    st.lo = l;
+    st.hi = h;
+    return st;
+}
+
+// Counts of every node in all threads' view (s_tot), from the 32-row partials of a
+// pass, by one block.  The order of the additions is fixed and the same whatever the
+// number of halvings per pass: four row blocks in turn (128 rows), then the tree over
+// 64 such sums, then those trees in turn.
+// Most rows of the two forms.  Eight halvings per pass at 1250 rows take as long as four
+// (a tail of 238 and 231 us); 8192 rows are one tree of 64 sums per node, and at 10,000
+// a second tree in every block is worth no more than a launch (318 and 326 us).
+constexpr long FT_DEEP = 1024, FT_FUSED = 8192;
+
+template <int LEVELS>
+__device__ inline void tree_totals(unsigned n_rb, const double *__restrict__ part, double *s_tot)
+{
+    constexpr int NODES = ft_nodes(LEVELS), NW = DT / 64;
+    if constexpr (LEVELS == 8) {                              // a thread per node
+        constexpr int SUMS = FT_DEEP / 128;
+        static_assert(SUMS <= 64, "one tree");
+        double v[SUMS];
+#pragma unroll
+        for (int q = 0; q < SUMS; ++q) {
+            double x[4];
+#pragma unroll
+            for (unsigned e = 0; e < 4; ++e) x[e] = part[ft_at<LEVELS>(0, min(4u * q + e, n_rb - 1), threadIdx.x)];
+            v[q] = 0.0;
+#pragma unroll
+            for (unsigned e = 0; e < 4; ++e) v[q] += 4u * q + e < n_rb ? x[e] : 0.0;
+        }
+#pragma unroll
+        for (int o = SUMS / 2; o > 0; o >>= 1)
+#pragma unroll
+            for (int q = 0; q < o; ++q) v[q] += v[q + o];
+        s_tot[threadIdx.x] = v[0];
+    } else {                                                  // a wave per node, a lane per sum
+        constexpr int PER = (NODES + NW - 1) / NW, TREES = FT_FUSED / (128 * 64);
+        const unsigned lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+        double v[TREES][PER];
+#pragma unroll
+        for (int w = 0; w < TREES; ++w)
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                double x[4];
+#pragma unroll
+                for (unsigned e = 0; e < 4; ++e)
+                    x[e] = part[ft_at<LEVELS>(ft_pitch(n_rb), min(4 * (64 * w + lane) + e, n_rb - 1),
+                                              min((int)(wv + i * NW), NODES - 1))];
+                v[w][i] = 0.0;
+#pragma unroll
+                for (unsigned e = 0; e < 4; ++e) v[w][i] += 4 * (64 * w + lane) + e < n_rb ? x[e] : 0.0;
+            }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < TREES; ++w) {
+                for (int o = 32; o > 0; o >>= 1) v[w][i] += __shfl_xor(v[w][i], o);
+                t += v[w][i];
+            }
+            if (lane == 0 && wv + i * NW < NODES) s_tot[wv + i * NW] = t;
+        }
+    }
+    __syncthreads();
+}
+
+// State at the start of pass `pass` in every thread: the bracket of the block
+// partials `prev` (pass 0), or the previous pass's state and partials.
+template <int LEVELS>
+__device__ inline FermiState tree_state(int pass, unsigned n_rb, unsigned n_bracket, double n_elec,
+                                        const double *__restrict__ prev, const FermiState *st, double *s_tot,
+                                        FermiState *s_st)
+{
+    if (pass == 0) {
+        const double L = partials_combine(prev, n_bracket, 2, 0, 1, s_tot);
+        const double H = partials_combine(prev, n_bracket, 2, 1, 2, s_tot);
+        if (threadIdx.x == 0) *s_st = FermiState{L, H, 0.0, 0.0};
+    } else {
+        const FermiState was = st[pass - 1];
+        if (was.done != 0.0) return was;                     // the same in every thread
+        tree_totals<LEVELS>(n_rb, prev, s_tot);
+        if (threadIdx.x == 0) *s_st = tree_descend(was, LEVELS, n_elec, s_tot);
+    }
+    __syncthreads();
+    return *s_st;
+}
+
+// One pass.  A row's count at an energy is Clenshaw's recurrence over its 200 or so
+// coefficients, one multiply-add after the other, so a pass is as short as the
+// loads before it and the nodes beside it allow:
+//  * 32 rows' coefficients are staged in LDS, FP_CH terms at a time, every thread's
+//    loads in flight at once (a recurrence that loads as it goes waited for memory
+//    every few terms), as the terms w_k = (g_(k-2) - g_k) / k;
+//  * the block's threads are 32 rows x 8 groups of nodes, so a wave reads each term
+//    once per row from LDS, without conflicts;
+//  * up to FT_DEEP rows a pass takes eight halvings (255 nodes, on eight times the
+//    blocks), as fewer rows leave the chip idle at the 15 nodes of four;
+//  * FUSED: the block first replays the previous pass's decisions itself, from its
+//    partials, where those are few enough for every block to read; otherwise
+//    k_fermi_pick does so in a launch between the passes.  (A last block that
+//    did it at the end of the pass would need a device-scope fence in every block,
+//    which writes back L2.)
+// A whole search of 640 rows, 200 terms: 16 passes of 29 us and 16 decisions of 5 -> 8
+// passes of 16; 5120 rows: the same -> 16 passes of 12; 40,960 rows: 16 of 42 + 5 -> 16
+// of 26 + 7 (an empty launch shows 4.5).
+template <int LEVELS, bool FUSED>
+__global__ void __launch_bounds__(DT)
+k_fermi_pass(int n_rows, int n_exp, int pass, unsigned n_bracket, double n_elec, const double *__restrict__ gs,
+             const double *__restrict__ a_inf, const double *__restrict__ b_inf, const double *__restrict__ prev,
+             double *__restrict__ part, FermiState *st)
+{
+    constexpr int NODES = ft_nodes(LEVELS);
+    constexpr int NPT = LEVELS == 8 ? 4 : 2;                 // nodes per thread
+    __shared__ double s_w[FP_CH * FP_ROWS], s_inv[FP_CH], s_part[FP_GROUPS * NPT];
+    __shared__ FermiState s_st;
+    const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS);
+    const int row = threadIdx.x & (FP_ROWS - 1), grp = threadIdx.x / FP_ROWS;
+    const int r = min((int)blockIdx.x * FP_ROWS + row, n_rows - 1);
+    const bool live = (int)blockIdx.x * FP_ROWS + row < n_rows;
+    const int K = n_exp + 2, nch = (K + FP_CH - 1) / FP_CH;
+    // g_(kb - 1 + FP_RUN grp + t), t = 0 .. FP_RUN + 1, of this thread's row, zero
+    // outside 0 .. n_exp, where kb = K - (c + 1) FP_CH: chunk c holds the terms
+    // k = kb + 1 .. kb + FP_CH, highest terms first
+    double g[FP_RUN + 2];
+    auto fetch = [&](int c) {
+        const int k0 = K - (c + 1) * FP_CH - 1 + FP_RUN * grp;
+        const double *q = gs + (long)k0 * n_rows + r;
+#pragma unroll
+        for (int t = 0; t < FP_RUN + 2; ++t, q += n_rows) {
+            const bool in = k0 + t >= 0 && k0 + t <= n_exp;
+            const double v = *(in ? q : gs);
+            g[t] = in ? v : 0.0;
+        }
+    };
+    FermiState now;
+    if constexpr (FUSED) {
+        fetch(0);                                            // comes while the decisions are replayed
+        now = tree_state<LEVELS>(pass, n_rb, n_bracket, n_elec, prev, st, s_w, &s_st);
+        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) st[pass] = now;
+        if (now.done != 0.0) return;
+    } else {
+        now = *st;
+        if (now.done != 0.0) return;
+        fetch(0);
+    }
+    const double ai = a_inf[r], bi = b_inf[r], g0 = gs[r];
+    // the group's nodes; those past the tree repeat its last one and are not kept
+    const int p0 = ((int)blockIdx.y * FP_GROUPS + grp) * NPT;
+    // sum_k w_k sin(k theta) = sin(theta) sum_k w_k U_(k-1)(cos theta), by
+    // Clenshaw's recurrence from the highest term down
+    double twoc[NPT], b1[NPT], b2[NPT];
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        const double eps = (tree_mid(now.lo, now.hi, min(p0 + j, NODES - 1) + 1) - ai) / (2.0 * bi);
+        twoc[j] = 2.0 * (eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps));
+        b1[j] = 0.0;
+        b2[j] = 0.0;
+    }
+    for (int c = 0; c < nch; ++c) {
+        const int kb = K - (c + 1) * FP_CH;
+        __syncthreads();                                     // the previous terms (or counts) are used
+        if (threadIdx.x < FP_CH) s_inv[threadIdx.x] = 1.0 / (double)max(kb + 1 + (int)threadIdx.x, 1);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < FP_RUN; ++t) {
+            const int i = FP_RUN * grp + t;
+            if (i < FP_CH) s_w[i * FP_ROWS + row] = (g[t] - g[t + 2]) * s_inv[i];
+        }
+        __syncthreads();
+        if (c + 1 < nch) fetch(c + 1);
+        const int i0 = max(0, -kb);
+#pragma unroll 8
+        for (int i = FP_CH - 1; i >= i0; --i) {
+            const double wk = s_w[i * FP_ROWS + row];
+#pragma unroll
+            for (int j = 0; j < NPT; ++j) {
+                const double bn = fma(twoc[j], b1[j], wk - b2[j]);
+                b2[j] = b1[j];
+                b1[j] = bn;
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        const double cc = 0.5 * twoc[j];
+        const double sn = sqrt(fmax(0.0, 1.0 - cc * cc));
+        double v = live ? g0 * (1.0 - acos(cc) / M_PI) + sn * b1[j] / M_PI : 0.0;
+        for (int o = FP_ROWS / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        if (row == 0) s_part[grp * NPT + j] = v;
+    }
+    __syncthreads();
+    const int p = (int)blockIdx.y * FP_GROUPS * NPT + threadIdx.x;
+    if (threadIdx.x < FP_GROUPS * NPT && p < NODES) part[ft_at<LEVELS>(ft_pitch(n_rb), blockIdx.x, p)] = s_part[threadIdx.x];
+}
+
+// The pass over so many rows that the chip is full: two lanes share an orbital row,
+// lane h of the pair taking nodes 8h .. 8h+7 (the last lane 7 nodes), both reading
+// the same coefficients as they go; no LDS copy and an eighth of the waves' starts
+// and ends per row.  Partials of 128 rows.
+constexpr int FT_LEVELS = 4, FT_NODES = ft_nodes(FT_LEVELS), FT_HALF = (FT_NODES + 1) / 2;
 
 __global__ void __launch_bounds__(DT)
 k_fermi_tree(int n_rows, int n_exp, const double *__restrict__ gs, const double *__restrict__ a_inf,
@@ -494,12 +835,10 @@ k_fermi_tree(int n_rows, int n_exp, const double *__restrict__ gs, const double 
         // before and after it), which keeps the kernel's registers low
         double twoc[FT_HALF], b1[FT_HALF], b2[FT_HALF];
         {
-            double mid[FT_NODES];
-            tree_points(lo, hi, mid);
 #pragma unroll
             for (int j = 0; j < FT_HALF; ++j) {
                 const int p = h * FT_HALF + j < FT_NODES ? h * FT_HALF + j : FT_NODES - 1;
-                double eps = (mid[p] - ai) / (2.0 * bi);
+                double eps = (tree_mid(lo, hi, p + 1) - ai) / (2.0 * bi);
                 twoc[j] = 2.0 * (eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps));
                 b1[j] = 0.0;
                 b2[j] = 0.0;
@@ -509,7 +848,7 @@ k_fermi_tree(int n_rows, int n_exp, const double *__restrict__ gs, const double 
         // Clenshaw's recurrence from the highest term down; w_k = (g_(k-2) - g_k) / k
         // (w_1 = -g_1), with g_k = 0 beyond n_exp
         double gk = 0.0, gkm1 = 0.0;
-#pragma unroll 4
+#pragma unroll 8
         for (int k = n_exp + 2; k >= 1; --k) {
             const double gkm2 = (k >= 2) ? gs[(long)(k - 2) * n_rows + r] : 0.0;
             const double wk = ((k >= 2) ? (gkm2 - gk) : -gk) * s_inv[k];
@@ -538,110 +877,227 @@ k_fermi_tree(int n_rows, int n_exp, const double *__restrict__ gs, const double 
 #pragma unroll
         for (int p = 0; p < FT_NODES; ++p) v[p] = (h == p / FT_HALF) ? cnt[p % FT_HALF] : 0.0;
         const double t = block_sum_n<FT_NODES>(v, s_red);
-        if (threadIdx.x < FT_NODES) part[(size_t)FT_NODES * blockIdx.x + threadIdx.x] = t;
+        if (threadIdx.x < FT_NODES) part[ft_at<FT_LEVELS>(gridDim.x, blockIdx.x, threadIdx.x)] = t;
     }
 }
 
-// The pass's decisions, in a launch of its own (one block) so that no block
-// of the pass needs a device-scope fence: the block partials of every node
-// are summed in a fixed order (thread t takes blocks t, t + DT, ..., then the
-// fixed wave tree), and the four decisions are replayed (count < n_elec:
-// lo = mid, else hi = mid), stopping when a midpoint equals an end of its
-// bracket or after the most halvings plain bisection takes.
-__global__ void __launch_bounds__(DT)
-k_fermi_pick(unsigned n_blocks, double n_elec, const double *__restrict__ part, FermiState *st)
+// The decisions of a pass whose partials are many, in a launch of its own (one
+// block): every node's sums (Q partials in turn) in a fixed order, thread t of DT
+// taking sums t, t + DT, ..., then the fixed tree.  The nodes are dealt to FT_PICK such
+// sets of threads, and a thread's loads are in flight together: one block waits for
+// memory, not for its bandwidth.
+constexpr int FT_PICK = 4;
+
+template <int Q>
+__global__ void __launch_bounds__(FT_PICK * DT)
+k_fermi_pick(unsigned n_rb, double n_elec, const double *__restrict__ part, FermiState *st)
 {
-    __shared__ double s_red[FT_NODES * (DT / 64)], s_tot[FT_NODES];
+    constexpr int NPT = (FT_NODES + FT_PICK - 1) / FT_PICK, NW = DT / 64, AHEAD = 8 / Q;
+    __shared__ double s_red[FT_PICK][NPT * NW], s_tot[FT_PICK * NPT];
     if (st->done != 0.0) return;
-    const double lo = st->lo, hi = st->hi;
-    double acc[FT_NODES];
+    const unsigned t = threadIdx.x % DT, set = threadIdx.x / DT, n = (n_rb + Q - 1) / Q;
+    const size_t pitch = Q == 1 ? n_rb : ft_pitch(n_rb);
+    double acc[NPT];
 #pragma unroll
-    for (int p = 0; p < FT_NODES; ++p) acc[p] = 0.0;
-    for (unsigned q = threadIdx.x; q < n_blocks; q += blockDim.x)
+    for (int p = 0; p < NPT; ++p) acc[p] = 0.0;
+    for (unsigned q0 = t; q0 < n; q0 += AHEAD * DT) {
+        double x[AHEAD][NPT][Q];
 #pragma unroll
-        for (int p = 0; p < FT_NODES; ++p) acc[p] += part[(size_t)q * FT_NODES + p];
-    const double t = block_sum_n<FT_NODES>(acc, s_red);
-    if (threadIdx.x < FT_NODES) s_tot[threadIdx.x] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double tot[FT_NODES];
+        for (int i = 0; i < AHEAD; ++i)
 #pragma unroll
-        for (int p = 0; p < FT_NODES; ++p) tot[p] = s_tot[p];
-        double mid[FT_NODES];
-        tree_points(lo, hi, mid);
-        double l = lo, hh = hi;
-        int node = 1;
-        double nh = st->halvings;
-        for (int lev = 0; lev < FT_LEVELS; ++lev) {
-            const double m = mid[node - 1];
-            if (nh >= FT_MAX_HALVINGS || m <= l || m >= hh) { st->done = 1.0; break; }
-            if (2.0 * tot[node - 1] < n_elec) { l = m; node = 2 * node + 1; }
-            else { hh = m; node = 2 * node; }
-            nh += 1.0;
-        }
-        st->lo = l;
-        st->hi = hh;
-        st->halvings = nh;
+            for (int p = 0; p < NPT; ++p)
+#pragma unroll
+                for (unsigned e = 0; e < Q; ++e)
+                    x[i][p][e] = part[ft_at<FT_LEVELS>(pitch, min(Q * (q0 + i * DT) + e, n_rb - 1),
+                                                       min((int)set * NPT + p, FT_NODES - 1))];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+            for (int p = 0; p < NPT; ++p) {
+                double v = 0.0;
+#pragma unroll
+                for (unsigned e = 0; e < Q; ++e) v += Q * (q0 + i * DT) + e < n_rb ? x[i][p][e] : 0.0;
+                acc[p] += v;
+            }
     }
+#pragma unroll
+    for (int p = 0; p < NPT; ++p)
+        for (int o = 32; o > 0; o >>= 1) acc[p] += __shfl_xor(acc[p], o);
+    if ((t & 63) == 0) {
+#pragma unroll
+        for (int p = 0; p < NPT; ++p) s_red[set][p * NW + (t >> 6)] = acc[p];
+    }
+    __syncthreads();
+    if (t < NPT) {
+        double v = 0.0;
+        for (int q = 0; q < NW; ++q) v += s_red[set][t * NW + q];
+        s_tot[set * NPT + t] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) *st = tree_descend(*st, FT_LEVELS, n_elec, s_tot);
 }
 
-__global__ void k_fermi_finish(FermiState *st, double *E_F)
+__global__ void k_fermi_finish(const FermiState *st, double *E_F)
 {
     E_F[0] = 0.5 * (st->lo + st->hi);
 }
 
-// per-atom N, U, n(E_F) and block partials of U.  One thread per orbital row
-// (EA atoms x n_orb rows per block, so the GPU has enough waves for the long
-// per-row sums); an atom's orbitals are then added in orbital order, as a
-// per-atom loop would add them.
-constexpr int EA = 64;           // atoms per block of the energy pass
+// the last pass's decisions and the level (one block)
+template <int LEVELS>
+__global__ void __launch_bounds__(DT)
+k_fermi_finish_fused(unsigned n_rb, double n_elec, int pass, const double *__restrict__ prev, const FermiState *st,
+                     double *E_F)
+{
+    __shared__ double s_tot[256];
+    __shared__ FermiState s_st;
+    const FermiState now = tree_state<LEVELS>(pass, n_rb, 0, n_elec, prev, st, s_tot, &s_st);
+    if (threadIdx.x == 0) E_F[0] = 0.5 * (now.lo + now.hi);
+}
 
-__global__ void __launch_bounds__(EA * 9)
+// The search over n_rows rows, where each block replays the previous decisions.
+// `tree` holds the partials of two passes in turn and the states of all; NULL where the
+// caller's workspace has no room for it.
+template <int LEVELS>
+static void fermi_search_fused(int n_rows, int n_exp, double n_elec, const double *gs, const double *a_inf,
+                               const double *b_inf, unsigned n_bracket, const double *bracket, double *tree,
+                               FermiState *st, double *E_F, hipStream_t stream)
+{
+    constexpr int NPT = LEVELS == 8 ? 4 : 2, PER_Y = FP_GROUPS * NPT, PASSES = (FT_MAX_HALVINGS + LEVELS - 1) / LEVELS;
+    const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS);
+    const dim3 grid(n_rb, (ft_nodes(LEVELS) + PER_Y - 1) / PER_Y);
+    double *buf[2] = {tree, tree + ft_pitch(n_rb) * (ft_nodes(LEVELS) + 1)};
+    for (int it = 0; it < PASSES; ++it)
+        k_fermi_pass<LEVELS, true><<<grid, DT, 0, stream>>>(n_rows, n_exp, it, n_bracket, n_elec, gs, a_inf, b_inf,
+                                                               it ? buf[(it - 1) & 1] : bracket, buf[it & 1], st);
+    k_fermi_finish_fused<LEVELS><<<1, DT, 0, stream>>>(n_rb, n_elec, PASSES, buf[(PASSES - 1) & 1], st, E_F);
+}
+
+static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs, const double *a_inf,
+                         const double *b_inf, unsigned n_bracket, double *part, double *tree, FermiState *st,
+                         double *E_F, hipStream_t stream)
+{
+    const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS), n_tb = (unsigned)((2L * n_rows + DT - 1) / DT);
+    k_bracket_pick<<<1, DT, 0, stream>>>(n_bracket, part, st);
+    for (int it = 0; it < FT_MAX_HALVINGS / FT_LEVELS; ++it) {
+        if (tree) {
+            k_fermi_pass<FT_LEVELS, false><<<n_rb, DT, 0, stream>>>(n_rows, n_exp, it, 0, n_elec, gs, a_inf, b_inf,
+                                                                    nullptr, tree, st);
+            k_fermi_pick<4><<<1, FT_PICK * DT, 0, stream>>>(n_rb, n_elec, tree, st);
+        } else {
+            k_fermi_tree<<<n_tb, DT, 0, stream>>>(n_rows, n_exp, gs, a_inf, b_inf, part, st);
+            k_fermi_pick<1><<<1, FT_PICK * DT, 0, stream>>>(n_tb, n_elec, part, st);
+        }
+    }
+    k_fermi_finish<<<1, 1, 0, stream>>>(st, E_F);
+}
+
+// Rows up to which k_fermi_pass makes the search's passes, k_fermi_tree beyond: 26 us
+// against 42 at 40,960 rows, 101 against 76 at 138,240.
+constexpr long FT_SPREAD = 65536;
+
+// per-atom N, U, n(E_F) and block partials of U.  A row's sums over its 200 or so
+// terms are split over EN_SEGS threads, each starting its run of terms from its own
+// power of the rotation, with the run's coefficients in flight together: a single thread
+// per row waits for one memory access after another and for one rotation after another.
+// An atom's orbitals are then added in orbital order, as a per-atom loop would
+// add them.  200 terms: 128 atoms 69 -> 8 us, 8192 atoms 75 -> 19, 128,000 atoms 295 ->
+// 225 (its coefficients at 4.6 TB/s); eight runs per row instead of four: 7, 28 and 459.
+constexpr int EN_SEGS = 4, EN_RUN = 13;          // runs per row, coefficients loaded at once
+// atoms per block
+__host__ __device__ constexpr int en_atoms(int no) { return no <= 2 ? 16 : 8; }
+constexpr int EN_MAXT = 8 * 9 * EN_SEGS;
+constexpr int EN_TAB = 3 + EN_SEGS + EN_RUN;     // table entries past n_exp that the last run can reach
+
+__global__ void __launch_bounds__(EN_MAXT)
 k_energy(int n_atoms, int no, int n_exp, double wt, const double *__restrict__ gs, const double *__restrict__ a_inf,
          const double *__restrict__ b_inf, const double *__restrict__ H_on, const double *__restrict__ E_F,
          double *__restrict__ N_atom, double *__restrict__ U_atom, double *__restrict__ dos_atom,
          int *__restrict__ flags, double *__restrict__ part)
 {
-    __shared__ double s_inv[1040], s_red[EA * 9 / 64], s_n[EA * 9], s_u[EA * 9], s_d[EA * 9];
-    for (int k = threadIdx.x; k <= n_exp + 4; k += blockDim.x) s_inv[k] = k ? 1.0 / k : 0.0;
-    __syncthreads();
-    const double E = E_F[0];
+    __shared__ double s_inv[1024 + EN_TAB], s_s[3][EN_MAXT], s_red[EN_MAXT / 64];
+    const int EA = en_atoms(no), RB = EA * no;
+    const int row = threadIdx.x % RB, seg = threadIdx.x / RB;
     const long n_rows = (long)n_atoms * no;
-    const long r = (long)blockIdx.x * EA * no + threadIdx.x;
+    const long r = (long)blockIdx.x * RB + row;
+    const bool live = r < n_rows;
+    const long rr = live ? r : n_rows - 1;
+    const int T = (n_exp + EN_SEGS) / EN_SEGS;   // of the n_exp + 1 terms, per run
+    const int m0 = seg * T, m1 = min(m0 + T, n_exp + 1);
+    double g[EN_RUN];
+    auto fetch = [&](int m) {
+#pragma unroll
+        for (int t = 0; t < EN_RUN; ++t) {
+            const double v = gs[(long)min(m + t, n_exp) * n_rows + rr];
+            g[t] = m + t < m1 ? v : 0.0;
+        }
+    };
+    fetch(m0);
+    const double E = E_F[0], ai = a_inf[rr], bi = b_inf[rr];
+    for (int k = threadIdx.x; k < n_exp + EN_TAB; k += blockDim.x) s_inv[k] = k ? 1.0 / k : 0.0;
+    const double eps = (E - ai) / (2.0 * bi);
+    const double c = eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps);
+    const double s = sqrt(fmax(0.0, 1.0 - c * c));
+    const double c2 = c * c - s * s, s2 = 2.0 * c * s;
+    // pi chi^_1, chi^_(m+2) = (sin((m+3) phi)/(m+3) - sin((m+1) phi)/(m+1)) / pi
+    const double x1 = (M_PI - acos(c)) + 0.5 * s2;
+    // (cos, sin)(m0 phi) by squarings
+    double C = 1.0, S = 0.0;
+    {
+        double pc = c, ps = s;
+        for (int e = m0; e; e >>= 1) {
+            if (e & 1) {
+                const double t = C * pc - S * ps;
+                S = S * pc + C * ps;
+                C = t;
+            }
+            const double t = pc * pc - ps * ps;
+            ps = 2.0 * pc * ps;
+            pc = t;
+        }
+    }
+    __syncthreads();
+    // sin((m+1) phi), sin((m+2) phi) and (cos, sin)((m+3) phi), advanced by
+    // unit-modulus rotation; pi chi^_m, pi chi^_(m+1) carried along
+    double w1 = S * c + C * s, w2 = S * c2 + C * s2;
+    double c3 = (C * c2 - S * s2) * c - w2 * s, w3 = w2 * c + (C * c2 - S * s2) * s;
+    double chi0 = m0 == 0 ? 0.0 : (m0 == 1 ? x1 : w1 * s_inv[m0 + 1] - (S * c - C * s) * s_inv[max(m0 - 1, 0)]);
+    double chi1 = m0 == 0 ? x1 : w2 * s_inv[m0 + 2] - S * s_inv[m0];
     double N = 0.0, U = 0.0, D = 0.0;
-    if (r < n_rows) {
-        double ai = a_inf[r], bi = b_inf[r];
-        double eps = (E - ai) / (2.0 * bi);
-        double c = eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps);
-        double s = sqrt(fmax(0.0, 1.0 - c * c));
-        double phi = acos(c);
-        // sin((m+1) phi), sin((m+2) phi) and (cos, sin)((m+3) phi), advanced
-        // by unit-modulus rotation; chi^_m, chi^_(m+1) carried along
-        const double c2 = c * c - s * s, s2 = 2.0 * c * s;
-        double w1 = s, w2 = s2;
-        double c3 = c2 * c - s2 * s, w3 = s2 * c + c2 * s;
-        double chi0 = 0.0;
-        double chi1 = 1.0 - phi / M_PI + s2 / (2.0 * M_PI);
-#pragma unroll 8
-        for (int m = 0; m <= n_exp; ++m) {
-            // chi^_(m+2) = (sin((m+3) phi)/(m+3) - sin((m+1) phi)/(m+1)) / pi
-            double chi2 = (w3 * s_inv[m + 3] - w1 * s_inv[m + 1]) / M_PI;
-            double g = gs[(long)m * n_rows + r];
-            N = fma(g, chi1, N);
-            U = fma(g, chi2 + chi0, U);
-            D = fma(g, w1, D);
+    for (int mb = m0;;) {
+#pragma unroll
+        for (int t = 0; t < EN_RUN; ++t) {
+            const int m = mb + t;
+            const double chi2 = w3 * s_inv[m + 3] - w1 * s_inv[m + 1];
+            N = fma(g[t], chi1, N);
+            U = fma(g[t], chi2 + chi0, U);
+            D = fma(g[t], w1, D);
             chi0 = chi1;
             chi1 = chi2;
-            double nc = c3 * c - w3 * s, ns = w3 * c + c3 * s;
+            const double nc = c3 * c - w3 * s, ns = w3 * c + c3 * s;
             w1 = w2; w2 = w3; w3 = ns; c3 = nc;
         }
-        U = bi * U + (ai - H_on[r]) * N;
-        D = (eps > -1.0 && eps < 1.0) ? D / (M_PI * bi) : 0.0;
-        if (!(eps > -1.0 && eps < 1.0)) flags[r] |= BOP_FLAG_OUTSIDE;
+        mb += EN_RUN;
+        if (mb - m0 >= T) break;                 // the same for every thread
+        fetch(mb);
     }
-    s_n[threadIdx.x] = N;
-    s_u[threadIdx.x] = U;
-    s_d[threadIdx.x] = D;
+    s_s[0][threadIdx.x] = N;
+    s_s[1][threadIdx.x] = U;
+    s_s[2][threadIdx.x] = D;
+    __syncthreads();
+    if (seg == 0) {
+        for (int q = 1; q < EN_SEGS; ++q) {
+            N += s_s[0][q * RB + row];
+            U += s_s[1][q * RB + row];
+            D += s_s[2][q * RB + row];
+        }
+        N /= M_PI;
+        U = bi * (U / M_PI) + (ai - H_on[rr]) * N;
+        D = (eps > -1.0 && eps < 1.0) ? D / (M_PI * bi) : 0.0;
+        if (live && !(eps > -1.0 && eps < 1.0)) flags[r] |= BOP_FLAG_OUTSIDE;
+        s_s[0][row] = N;
+        s_s[1][row] = U;
+        s_s[2][row] = D;
+    }
     __syncthreads();
     const int t = threadIdx.x;
     const long i = (long)blockIdx.x * EA + t;
@@ -649,9 +1105,9 @@ k_energy(int n_atoms, int no, int n_exp, double wt, const double *__restrict__ g
     if (t < EA && i < n_atoms) {
         double sN = 0.0, sU = 0.0, sD = 0.0;
         for (int a = 0; a < no; ++a) {
-            sN += s_n[t * no + a];
-            sU += s_u[t * no + a];
-            sD += s_d[t * no + a];
+            sN += s_s[0][t * no + a];
+            sU += s_s[1][t * no + a];
+            sD += s_s[2][t * no + a];
         }
         // both spins; wt orbitals per row in the atom-averaged mode
         N_atom[i] = 2.0 * wt * sN;
@@ -675,7 +1131,10 @@ k_energy_total(unsigned n_blocks, const double *__restrict__ part, double *__res
 struct EnergyWs {
     double *gs, *part;
     FermiState *st;
-    size_t bytes;
+    size_t bytes;           // what every call needs
+    double *tree;           // the Fermi passes' 32-row partials (two passes in turn) and states, where n_rows <= FT_SPREAD
+    FermiState *states;
+    size_t bytes_tree;      // with these
 };
 
 EnergyWs carve(void *base, long n_rows, int n_exp)
@@ -684,10 +1143,16 @@ EnergyWs carve(void *base, long n_rows, int n_exp)
     char *p = (char *)base;
     auto take = [&](size_t b) { char *r = p; p += align_up(b, 256); return (void *)r; };
     w.gs = (double *)take(sizeof(double) * (size_t)(n_exp + 1) * (size_t)n_rows);
-    long nblk = 2 * ((n_rows + DT - 1) / DT) + 1;       // two lanes per row in the Fermi passes
-    w.part = (double *)take(sizeof(double) * FT_NODES * (size_t)nblk);
+    long nblk = 2 * ((n_rows + DT - 1) / DT) + 1;       // 128-row sums of the 15 nodes of four halvings
+    w.part = (double *)take(sizeof(double) * 15 * (size_t)nblk);
     w.st = (FermiState *)take(sizeof(FermiState));
     w.bytes = (size_t)(p - (char *)base);
+    if (n_rows <= FT_SPREAD) {
+        const size_t rb = ft_pitch((unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS));
+        w.tree = (double *)take(sizeof(double) * 2 * rb * (n_rows <= FT_DEEP ? 256 : 16));
+        w.states = (FermiState *)take(sizeof(FermiState) * (FT_MAX_HALVINGS + 1));
+    }
+    w.bytes_tree = (size_t)(p - (char *)base);
     return w;
 }
 
@@ -722,7 +1187,7 @@ extern "C" int bop_recursion(int n_rows, int n_max, const double *mu, int bw_mod
 extern "C" size_t bop_energy_workspace_size(int n_atoms, int n_orb, int n_exp)
 {
     if (n_atoms < 0 || n_orb <= 0 || n_exp < 0) return 0;
-    return carve(nullptr, (long)n_atoms * n_orb, n_exp).bytes + 256;
+    return carve(nullptr, (long)n_atoms * n_orb, n_exp).bytes_tree + 256;
 }
 
 // wt: orbitals each row stands for (1; n_orb in the atom-averaged mode, where
@@ -748,24 +1213,28 @@ static int energy_impl(int n_atoms, int no, int n_max, int n_exp, const double *
                 "bop_energy: n_elec outside [0, 2 n_rows]");
     const unsigned nblk = (unsigned)((R + DT - 1) / DT);
     const int L = (n_max - 1) / 2 + 1 > n_max / 2 ? (n_max - 1) / 2 + 1 : n_max / 2;
-    if (L <= 11) k_dos_coeffs<11><<<nblk, DT, 0, stream>>>((int)R, n_max, n_exp, mu, a, b, a_inf, b_inf, w.gs, flags);
+    if (n_max <= CL_NMAX && R <= CL_ROWS)
+        k_dos_coeffs_lanes<<<(unsigned)((R + CR - 1) / CR), DT, 0, stream>>>((int)R, n_max, n_exp, mu, a, b, a_inf, b_inf,
+                                                                             w.gs, flags);
+    else if (L <= 11) k_dos_coeffs<11><<<nblk, DT, 0, stream>>>((int)R, n_max, n_exp, mu, a, b, a_inf, b_inf, w.gs, flags);
     else k_dos_coeffs<21><<<nblk, DT, 0, stream>>>((int)R, n_max, n_exp, mu, a, b, a_inf, b_inf, w.gs, flags);
     BOP_LAUNCHED();
     if (ef_mode == 0) {
         k_bracket<<<nblk, DT, 0, stream>>>((int)R, a_inf, b_inf, w.part);
-        k_bracket_pick<<<1, DT, 0, stream>>>(nblk, w.part, w.st);
-        BOP_LAUNCHED();
-        const unsigned fblk = (unsigned)((2 * R + DT - 1) / DT);
-        for (int it = 0; it < FT_PASSES; ++it) {
-            k_fermi_tree<<<fblk, DT, 0, stream>>>((int)R, n_exp, w.gs, a_inf, b_inf, w.part, w.st);
-            k_fermi_pick<<<1, DT, 0, stream>>>(fblk, n_elec / wt, w.part, w.st);
-        }
-        BOP_LAUNCHED();
-        k_fermi_finish<<<1, 1, 0, stream>>>(w.st, E_F);
+        // a workspace without the tree's partials (of the size earlier versions asked
+        // for, or the fixed array at its limit) takes the route of many rows
+        const double ne = n_elec / wt;
+        const bool tree = R <= FT_SPREAD && ws_bytes >= w.bytes_tree;
+        if (tree && R <= FT_DEEP)
+            fermi_search_fused<8>((int)R, n_exp, ne, w.gs, a_inf, b_inf, nblk, w.part, w.tree, w.states, E_F, stream);
+        else if (tree && R <= FT_FUSED)
+            fermi_search_fused<4>((int)R, n_exp, ne, w.gs, a_inf, b_inf, nblk, w.part, w.tree, w.states, E_F, stream);
+        else
+            fermi_search((int)R, n_exp, ne, w.gs, a_inf, b_inf, nblk, w.part, tree ? w.tree : nullptr, w.st, E_F, stream);
         BOP_LAUNCHED();
     }
-    const unsigned ablk = (unsigned)((n_atoms + EA - 1) / EA);
-    k_energy<<<ablk, EA * no, 0, stream>>>(n_atoms, no, n_exp, wt, w.gs, a_inf, b_inf, H_on, E_F, N_atom, U_atom,
+    const unsigned ablk = (unsigned)((n_atoms + en_atoms(no) - 1) / en_atoms(no));
+    k_energy<<<ablk, en_atoms(no) * no * EN_SEGS, 0, stream>>>(n_atoms, no, n_exp, wt, w.gs, a_inf, b_inf, H_on, E_F, N_atom, U_atom,
                                       dos_atom, flags, w.part);
     k_energy_total<<<1, DT, 0, stream>>>(ablk, w.part, U_total);
     BOP_LAUNCHED();
