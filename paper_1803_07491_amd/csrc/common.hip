@@ -41,37 +41,63 @@ int device_cus() { return cached_attr(0, hipDeviceAttributeMultiprocessorCount, 
 int device_lds_per_block() { return cached_attr(1, hipDeviceAttributeMaxSharedMemoryPerBlock, 65536); }
 
 // ---------------------------------------------------------------------------
-// exclusive scan: 1024 items per block (256 threads x 4), block totals scanned
+// exclusive scan: up to SCAN_ONE items by one block in one launch (a launch costs more
+// than the scan of so few); else 4096 items per block, the block totals scanned
 // recursively, then added back.
 // ---------------------------------------------------------------------------
-constexpr int SCAN_T = 256, SCAN_I = 4, SCAN_CHUNK = SCAN_T * SCAN_I;
+constexpr int SCAN_T = 1024, SCAN_I = 4, SCAN_CHUNK = SCAN_T * SCAN_I;
+constexpr long SCAN_ONE = 8 * SCAN_CHUNK;
 
+// Exclusive prefix of v over the block, plus carry; total: the sum over the block.
+__device__ inline int block_prefix(int v, int carry, int *s_w, int &total)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int x = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o);
+        x += lane >= o ? y : 0;
+    }
+    __syncthreads();                  // the previous use of s_w is over
+    if (lane == 63) s_w[w] = x;
+    __syncthreads();
+    int below = 0;
+    total = 0;
+    for (int q = 0; q < SCAN_T / 64; ++q) {
+        below += q < w ? s_w[q] : 0;
+        total += s_w[q];
+    }
+    return carry + below + x - v;
+}
+
+// One chunk per block; with sums == NULL one block takes all chunks in turn and writes
+// the total out[n].
 __global__ void __launch_bounds__(SCAN_T)
 scan_chunks(const int *__restrict__ in, int *__restrict__ out, long n, int *__restrict__ sums)
 {
-    __shared__ int s[SCAN_T];
-    long base = (long)blockIdx.x * SCAN_CHUNK + (long)threadIdx.x * SCAN_I;
-    int v[SCAN_I], t = 0;
-    for (int k = 0; k < SCAN_I; ++k) {
-        v[k] = (base + k < n) ? in[base + k] : 0;
-        t += v[k];
+    __shared__ int s_w[SCAN_T / 64];
+    int carry = 0;
+    for (long c = (long)blockIdx.x * SCAN_CHUNK; c < n; c += SCAN_CHUNK) {
+        const long base = c + (long)threadIdx.x * SCAN_I;
+        int v[SCAN_I], t = 0, total;
+        for (int k = 0; k < SCAN_I; ++k) {
+            v[k] = (base + k < n) ? in[base + k] : 0;
+            t += v[k];
+        }
+        int run = block_prefix(t, carry, s_w, total);
+        for (int k = 0; k < SCAN_I; ++k) {
+            if (base + k < n) out[base + k] = run;
+            run += v[k];
+        }
+        carry += total;
+        if (sums) break;
     }
-    s[threadIdx.x] = t;
-    __syncthreads();
-    for (int off = 1; off < SCAN_T; off <<= 1) {
-        int x = (threadIdx.x >= (unsigned)off) ? s[threadIdx.x - off] : 0;
-        __syncthreads();
-        s[threadIdx.x] += x;
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        if (sums) sums[blockIdx.x] = carry;
+        else out[n] = carry;
     }
-    int run = s[threadIdx.x] - t;   // exclusive prefix of this thread
-    for (int k = 0; k < SCAN_I; ++k) {
-        if (base + k < n) out[base + k] = run;
-        run += v[k];
-    }
-    if (threadIdx.x == SCAN_T - 1) sums[blockIdx.x] = s[SCAN_T - 1];
 }
 
+// adds the chunks' offsets; the last block writes the total out[n]
 __global__ void __launch_bounds__(SCAN_T)
 scan_add(int *__restrict__ out, long n, const int *__restrict__ offs)
 {
@@ -79,19 +105,13 @@ scan_add(int *__restrict__ out, long n, const int *__restrict__ offs)
     int o = offs[blockIdx.x];
     for (int k = 0; k < SCAN_I; ++k)
         if (base + k < n) out[base + k] += o;
-}
-
-__global__ void scan_total(int *__restrict__ out, long n, const int *__restrict__ in, const int *__restrict__ tot)
-{
-    // out[n] = out[n-1] + in[n-1]  (n >= 1), or the single-chunk total
-    if (n == 0) out[0] = 0;
-    else out[n] = tot ? tot[0] : out[n - 1] + in[n - 1];
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = offs[gridDim.x];
 }
 
 size_t scan_scratch_bytes(long n)
 {
     size_t b = 0;
-    while (n > 1) {
+    while (n > SCAN_ONE) {
         long nb = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
         b += align_up(sizeof(int) * (size_t)(2 * nb + 1), 256);
         n = nb;
@@ -101,8 +121,8 @@ size_t scan_scratch_bytes(long n)
 
 int exclusive_scan(const int *in, int *out, long n, void *scratch, hipStream_t stream)
 {
-    if (n <= 0) {
-        scan_total<<<1, 1, 0, stream>>>(out, 0, in, nullptr);
+    if (n <= SCAN_ONE) {
+        scan_chunks<<<1, SCAN_T, 0, stream>>>(in, out, n < 0 ? 0 : n, nullptr);
         BOP_LAUNCHED();
         return BOP_OK;
     }
@@ -110,19 +130,11 @@ int exclusive_scan(const int *in, int *out, long n, void *scratch, hipStream_t s
     int *sums = (int *)scratch;
     int *offs = sums + nb;
     char *next = (char *)scratch + align_up(sizeof(int) * (size_t)(2 * nb + 1), 256);
-    // the last element is needed for the total; read it before `out` may
-    // overwrite `in` (in == out is allowed)
     scan_chunks<<<(unsigned)nb, SCAN_T, 0, stream>>>(in, out, n, sums);
     BOP_LAUNCHED();
-    if (nb > 1) {
-        int rc = exclusive_scan(sums, offs, nb, next, stream);
-        if (rc) return rc;
-        scan_add<<<(unsigned)nb, SCAN_T, 0, stream>>>(out, n, offs);
-        BOP_LAUNCHED();
-        scan_total<<<1, 1, 0, stream>>>(out, n, in, offs + nb);
-    } else {
-        scan_total<<<1, 1, 0, stream>>>(out, n, in, sums);
-    }
+    int rc = exclusive_scan(sums, offs, nb, next, stream);
+    if (rc) return rc;
+    scan_add<<<(unsigned)nb, SCAN_T, 0, stream>>>(out, n, offs);
     BOP_LAUNCHED();
     return BOP_OK;
 }
