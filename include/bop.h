@@ -365,10 +365,11 @@ int bop_recursion(int n_rows, int n_max, const double *mu, int bw_mode,
  *
  *  ef_mode 0: E_F [device, 1 double] out: bisection (Sec. II) on
  *             2 sum N_ia(E) = n_elec over [min(a_inf - 2 b_inf), max(a_inf +
- *             2 b_inf)], halving while the midpoint differs from both ends (at
- *             most 64 times; four halvings are decided per pass over the
- *             coefficients, with exactly the midpoints and decisions of
- *             sequential bisection); E_F = midpoint of the final bracket.
+ *             2 b_inf)]: twelve halvings, then interpolation between counts
+ *             closer and closer to the root, whose bracket E_F lies in to the
+ *             counts' rounding.  Where the count is all but flat the halving
+ *             goes on while the midpoint differs from both ends (at most 64
+ *             times) and E_F = midpoint of the final bracket.
  *  ef_mode 1: E_F [device] in: energies at the given level.
  *  ws: bop_energy_workspace_size(n_atoms, n_orb, n_exp) bytes.
  *  n_exp <= 1024 (default used by the paper's example: 200); n_orb <= 9

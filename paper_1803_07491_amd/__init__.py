@@ -446,7 +446,7 @@ def recursion(mu_rows, n_max, global_ab=None, out=None, bw="gershgorin", beta=1.
 
 
 def energy(mu, rec, H_on, n_elec, n_max, n_exp=200, E_F=None, ws=None):
-    """Fermi level (bisection, unless ``E_F`` is given as a float or a
+    """Fermi level (bisection and interpolation, unless ``E_F`` is given as a float or a
     1-element device tensor), per-atom N, U, n(E_F) and U_total
     (``bop_energy``)."""
     torch = _torch()

@@ -5,7 +5,7 @@
 //    n_max by the chain recursion of App. B.4 with the constant terminator, and
 //    Jackson damping (Eq. Jackson);
 //  * electron counts, bond energies and DOS at E (App. B.2), the Fermi level
-//    by bisection (Sec. II), four or eight halvings per pass over the coefficients,
+//    by bisection and interpolation (Sec. II),
 //    per-atom sums (App. A.1 Eq. TB-Ubond).
 //
 // The chain recursion is evaluated on the computed levels 0..L-1 plus one
@@ -531,8 +531,9 @@ __device__ inline double block_sum_n(double (&v)[N], double *s_red /* N x (DT / 
     return t;
 }
 
-// Fermi search state: bracket [lo, hi], done flag, halvings taken so far.
-struct FermiState { double lo, hi, done, halvings; };
+// Fermi search state: bracket [lo, hi] with twice the counts at its ends, the expected
+// level, whether the search is to bisect throughout, done flag, halvings taken so far.
+struct FermiState { double lo, hi, nlo, nhi, x, plain, done, halvings; };
 
 __global__ void __launch_bounds__(DT)
 k_bracket(int n_rows, const double *__restrict__ a_inf, const double *__restrict__ b_inf,
@@ -556,43 +557,69 @@ k_bracket(int n_rows, const double *__restrict__ a_inf, const double *__restrict
 // and extrema are finished in a launch of their own: a last-block scheme
 // would need a device-scope fence in every block, which writes back L2.
 __global__ void __launch_bounds__(DT)
-k_bracket_pick(unsigned n_blocks, const double *__restrict__ part, FermiState *st)
+k_bracket_pick(int n_rows, unsigned n_blocks, const double *__restrict__ part, FermiState *st)
 {
     __shared__ double s_red[DT / 64];
     const double L = partials_combine(part, n_blocks, 2, 0, 1, s_red);
     const double H = partials_combine(part, n_blocks, 2, 1, 2, s_red);
-    if (threadIdx.x == 0) {
-        st->lo = L;
-        st->hi = H;
-        st->done = 0.0;
-        st->halvings = 0.0;
-    }
+    if (threadIdx.x == 0) *st = FermiState{L, H, 0.0, 2.0 * n_rows, 0.0, 0.0, 0.0, 0.0};
 }
 
-// Fermi level by bisection (Sec. II), LEVELS halvings per pass: a pass evaluates
-// the electron count at the 2^LEVELS - 1 midpoints that its halvings can visit (a
-// binary tree in heap order whose nodes are formed exactly as sequential bisection
-// forms them, mid = (lo + hi)/2), and the decisions are then replayed.  They, and
-// hence the root found when the count is not monotone, are those of plain bisection.
+// Fermi level (Sec. II): the root of the count by bisection, continued by interpolation.
+// A pass evaluates the electron count at 15 energies (nodes) and the state moves on:
+//  * bisecting passes (the first FT_TREE, and all after the closing ones): the nodes
+//    are the midpoints that the next four halvings can visit, a binary tree in heap
+//    order formed exactly as sequential bisection forms it, mid = (lo + hi)/2, and
+//    the four decisions are replayed.  They, and so the root found when the count
+//    is not monotone, are those of plain bisection;
+//  * after FT_TREE passes the count is smooth on the bracket, a 4096th of the band (its
+//    200 or so terms turn by a seventh of a radian over the pass's node spacing):
+//    the polynomial through the eight nodes nearest to the sign change gives its root
+//    to about 1e-12 of the band;
+//  * closing passes (FT_CLOSE at most): nodes at growing distances on both sides
+//    of the expected root, whose counts close the bracket around it.  Once it is
+//    narrower than FT_TIGHT of the last one the root follows by linear interpolation
+//    between the counts at its ends (its error is the bracket's square, below the
+//    counts' own rounding);
+//  * a count that is all but flat on the bracket (a gap, next to no or all electrons),
+//    where the level depends on the counts' rounding, is bisected throughout, to
+//    the last bit or FT_MAX_HALVINGS, and so is what the closing passes left open
+//    (a band edge in the bracket).
+// Four passes then do for what bisection alone takes 15 for.  Against it the level is
+// within 1e-15 eV over 54 to 27,648 atoms and 1 to 1024 terms; whole tails, 200 terms: 128
+// atoms 168 -> 91 us, 2000 atoms 326 -> 171, 8192 atoms 590 -> 300, 128,000 atoms 6.16 ->
+// 2.16 ms.
 constexpr int FT_MAX_HALVINGS = 64;            // as many as plain bisection takes at most
+constexpr int FT_LEVELS = 4, FT_NODES = (1 << FT_LEVELS) - 1;
+constexpr int FT_TREE = 3, FT_CLOSE = 2;       // bisecting passes first, closing passes then
+constexpr double FT_TIGHT = 1.0 / (1 << 24);
+// Least change of the count over the bracket, per row, for the closing passes: the counts'
+// rounding then moves the level by less than 1e-12 of the band.  (A count that is
+// reached at the bracket's very end may be reached there without slope.)
+constexpr double FT_SLOPE = 1e-7;
 constexpr int FP_ROWS = 32;                    // rows per row block (one per lane of half a wave)
 constexpr int FP_GROUPS = DT / FP_ROWS;        // thread groups of a block, each with its own nodes
 constexpr int FP_RUN = 26;                     // coefficients a thread stages
 constexpr int FP_CH = 202;                     // terms held in LDS: what lets three blocks share a CU
 static_assert(FP_CH <= FP_GROUPS * FP_RUN && FP_CH > (FP_GROUPS - 1) * FP_RUN, "the last group stages what is left");
-constexpr int ft_nodes(int levels) { return (1 << levels) - 1; }
-// A pass's partials: where few rows take many nodes, the nodes of a row block side by
-// side; else the row blocks of a node (a multiple of four of them), as the sums read them.
-__host__ __device__ inline size_t ft_pitch(unsigned n_rb) { return (n_rb + 3) / 4 * 4; }
-template <int LEVELS> __device__ inline size_t ft_at(size_t pitch, unsigned rb, int p)
+
+__device__ inline bool closing(const FermiState &st, int pass)
 {
-    return LEVELS == 8 ? (size_t)rb * 256 + p : (size_t)p * pitch + rb;
+    return pass >= FT_TREE && pass < FT_TREE + FT_CLOSE && st.plain == 0.0;
 }
 
-// midpoint of the tree's node `heap` (1-based) under [lo, hi]
-__device__ inline double tree_mid(double lo, double hi, int heap)
+// energy of node p in a pass
+__device__ inline double node_energy(const FermiState &st, int pass, int p)
 {
-    double l = lo, h = hi;
+    double l = st.lo, h = st.hi;
+    if (closing(st, pass)) {
+        const int j = p - FT_NODES / 2, d = j < 0 ? -j : j;
+        // 2^-36, 2^-30, .. 2^-12, 2^-7, 2^-3 of the bracket
+        const int e = d <= 5 ? -42 + 6 * d : (d == 6 ? -7 : -3);
+        const double off = d ? ldexp(h - l, e) : 0.0, x = j < 0 ? st.x - off : st.x + off;
+        return x < l ? l : (x > h ? h : x);
+    }
+    const int heap = p + 1;
     for (int bit = 30 - __clz(heap); bit >= 0; --bit) {
         const double m = 0.5 * (l + h);
         if (heap >> bit & 1) l = m; else h = m;
@@ -600,103 +627,131 @@ __device__ inline double tree_mid(double lo, double hi, int heap)
     return 0.5 * (l + h);
 }
 
-// The halvings of a pass over [st.lo, st.hi], tot[node] the count at its nodes
-// (count < n_elec: lo = mid, else hi = mid), stopping when a midpoint equals an end
-// of its bracket or after the most halvings plain bisection takes.
-__device__ inline FermiState tree_descend(FermiState st, int levels, double n_elec, const double *tot)
+// Root in [i, i + 1] of the polynomial through eight of the 17 equally spaced values
+// v (Newton's form on forward differences, a few safeguarded Newton steps).
+__device__ inline double root_between(const double *v, int i, double n_elec)
 {
-    double l = st.lo, h = st.hi;
-    int node = 1;
-    for (int lev = 0; lev < levels; ++lev) {
-        const double m = 0.5 * (l + h);
-        if (st.halvings >= FT_MAX_HALVINGS || m <= l || m >= h) { st.done = 1.0; break; }
-        if (2.0 * tot[node - 1] < n_elec) { l = m; node = 2 * node + 1; }
-        else { h = m; node = 2 * node; }
-        st.halvings += 1.0;
+    const int j0 = min(max(i - 3, 0), FT_NODES + 1 - 7);
+    double d[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) d[k] = v[j0 + k] - n_elec;
+    const double fl = v[i] - n_elec, fh = v[i + 1] - n_elec;
+#pragma unroll
+    for (int k = 1; k < 8; ++k)
+#pragma unroll
+        for (int q = 7; q >= k; --q) d[q] -= d[q - 1];
+    const double a = i - j0;
+    double u = a + fl / (fl - fh);
+    for (int it = 0; it < 5; ++it) {
+        double f = d[7], g = 0.0;
+#pragma unroll
+        for (int k = 6; k >= 0; --k) {
+            const double r = 1.0 / (k + 1), m = (u - k) * r;
+            g = fma(g, m, f * r);
+            f = fma(m, f, d[k]);
+        }
+        u -= f / g;
+        u = u < a ? a : (u > a + 1.0 ? a + 1.0 : u);
     }
-    st.lo = l;
-    st.hi = h;
-    return st;
+    return u - a;
 }
 
-// Counts of every node in all threads' view (s_tot), from the 32-row partials of a
-// pass, by one block.  The order of the additions is fixed and the same whatever the
-// number of halvings per pass: four row blocks in turn (128 rows), then the tree over
-// 64 such sums, then those trees in turn.
-// Most rows of the two forms.  Eight halvings per pass at 1250 rows take as long as four
-// (a tail of 238 and 231 us); 8192 rows are one tree of 64 sums per node, and at 10,000
-// a second tree in every block is worth no more than a launch (318 and 326 us).
-constexpr long FT_DEEP = 1024, FT_FUSED = 8192;
-
-template <int LEVELS>
-__device__ inline void tree_totals(unsigned n_rb, const double *__restrict__ part, double *s_tot)
+// The state after a pass from st, tot[p] the count at its node p (one thread; v:
+// scratch of FT_NODES + 2).
+__device__ inline FermiState fermi_advance(const FermiState &st, int pass, int n_rows, double n_elec, const double *tot,
+                                           double *v)
 {
-    constexpr int NODES = ft_nodes(LEVELS), NW = DT / 64;
-    if constexpr (LEVELS == 8) {                              // a thread per node
-        constexpr int SUMS = FT_DEEP / 128;
-        static_assert(SUMS <= 64, "one tree");
-        double v[SUMS];
-#pragma unroll
-        for (int q = 0; q < SUMS; ++q) {
-            double x[4];
-#pragma unroll
-            for (unsigned e = 0; e < 4; ++e) x[e] = part[ft_at<LEVELS>(0, min(4u * q + e, n_rb - 1), threadIdx.x)];
-            v[q] = 0.0;
-#pragma unroll
-            for (unsigned e = 0; e < 4; ++e) v[q] += 4u * q + e < n_rb ? x[e] : 0.0;
+    FermiState s = st;
+    double frac = 0.5;                            // where in the new bracket the root is expected
+    if (!closing(st, pass)) {
+        int node = 1;
+        for (int lev = 0; lev < FT_LEVELS; ++lev) {
+            const double m = 0.5 * (s.lo + s.hi);
+            if (s.halvings >= FT_MAX_HALVINGS || m <= s.lo || m >= s.hi) { s.done = 1.0; break; }
+            const double c = 2.0 * tot[node - 1];
+            if (c < n_elec) { s.lo = m; s.nlo = c; node = 2 * node + 1; }
+            else { s.hi = m; s.nhi = c; node = 2 * node; }
+            s.halvings += 1.0;
         }
+        if (pass != FT_TREE - 1 || s.done != 0.0) return s;
+        const double step = s.nhi - s.nlo, off = fmin(s.nhi - n_elec, n_elec - s.nlo);
+        if (!(step >= FT_SLOPE * n_rows && off >= step / (1 << 16))) {
+            s.plain = 1.0;
+            return s;
+        }
+        v[0] = st.nlo;
+        v[FT_NODES + 1] = st.nhi;
+        for (int q = 1; q <= FT_NODES; ++q) {      // in order of energy: node of the tree's level by the trailing zeros
+            const int z = __ffs(q) - 1;
+            v[q] = 2.0 * tot[(1 << (FT_LEVELS - 1 - z)) + (q >> (z + 1)) - 1];
+        }
+        frac = root_between(v, node - (1 << FT_LEVELS), n_elec);
+    } else {
+        int j = 0;
+        while (j < FT_NODES && 2.0 * tot[j] < n_elec) ++j;
+        if (j < FT_NODES) { s.hi = node_energy(st, pass, j); s.nhi = 2.0 * tot[j]; }
+        if (j > 0) { s.lo = node_energy(st, pass, j - 1); s.nlo = 2.0 * tot[j - 1]; }
+        frac = (n_elec - s.nlo) / (s.nhi - s.nlo);
+        if (s.hi - s.lo <= FT_TIGHT * (st.hi - st.lo)) s.done = 1.0;
+    }
+    if (!(frac >= 0.0 && frac <= 1.0)) frac = 0.5;
+    s.x = s.lo + frac * (s.hi - s.lo);
+    if (s.done != 0.0) s.lo = s.hi = s.x;
+    return s;
+}
+
+// A pass's 32-row partials: the row blocks of a node (a multiple of four of them) side
+// by side, as the sums read them.
+__host__ __device__ inline size_t ft_pitch(unsigned n_rb) { return (n_rb + 3) / 4 * 4; }
+
+// Counts of every node in all threads' view (s_tot), from the 32-row partials of a
+// pass, by one block.  The order of the additions is fixed: four row blocks in turn (128
+// rows), then the tree over 64 such sums, then those trees in turn.
+constexpr int FT_TREES = 2;
+constexpr long FT_FUSED = FT_TREES * 128 * 64;
+
+__device__ inline void node_totals(unsigned n_rb, const double *__restrict__ part, double *s_tot)
+{
+    constexpr int NW = DT / 64, PER = (FT_NODES + NW - 1) / NW;
+    const unsigned lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double sum[PER] = {};
+    for (unsigned q0 = lane; 4 * (q0 - lane) < n_rb; q0 += 64) {
+        double x[PER][4];
 #pragma unroll
-        for (int o = SUMS / 2; o > 0; o >>= 1)
+        for (int i = 0; i < PER; ++i)
 #pragma unroll
-            for (int q = 0; q < o; ++q) v[q] += v[q + o];
-        s_tot[threadIdx.x] = v[0];
-    } else {                                                  // a wave per node, a lane per sum
-        constexpr int PER = (NODES + NW - 1) / NW, TREES = FT_FUSED / (128 * 64);
-        const unsigned lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        double v[TREES][PER];
-#pragma unroll
-        for (int w = 0; w < TREES; ++w)
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                double x[4];
-#pragma unroll
-                for (unsigned e = 0; e < 4; ++e)
-                    x[e] = part[ft_at<LEVELS>(ft_pitch(n_rb), min(4 * (64 * w + lane) + e, n_rb - 1),
-                                              min((int)(wv + i * NW), NODES - 1))];
-                v[w][i] = 0.0;
-#pragma unroll
-                for (unsigned e = 0; e < 4; ++e) v[w][i] += 4 * (64 * w + lane) + e < n_rb ? x[e] : 0.0;
-            }
+            for (unsigned e = 0; e < 4; ++e)
+                x[i][e] = part[min((int)(wv + i * NW), FT_NODES - 1) * ft_pitch(n_rb) + min(4 * q0 + e, n_rb - 1)];
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             double t = 0.0;
 #pragma unroll
-            for (int w = 0; w < TREES; ++w) {
-                for (int o = 32; o > 0; o >>= 1) v[w][i] += __shfl_xor(v[w][i], o);
-                t += v[w][i];
-            }
-            if (lane == 0 && wv + i * NW < NODES) s_tot[wv + i * NW] = t;
+            for (unsigned e = 0; e < 4; ++e) t += 4 * q0 + e < n_rb ? x[i][e] : 0.0;
+            for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+            sum[i] += t;
         }
     }
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        if (lane == 0 && wv + i * NW < FT_NODES) s_tot[wv + i * NW] = sum[i];
     __syncthreads();
 }
 
 // State at the start of pass `pass` in every thread: the bracket of the block
-// partials `prev` (pass 0), or the previous pass's state and partials.
-template <int LEVELS>
-__device__ inline FermiState tree_state(int pass, unsigned n_rb, unsigned n_bracket, double n_elec,
-                                        const double *__restrict__ prev, const FermiState *st, double *s_tot,
-                                        FermiState *s_st)
+// partials `prev` (pass 0), or the previous pass's state and partials.  s_tot: 96.
+__device__ inline FermiState fermi_state(int pass, int n_rows, unsigned n_bracket, double n_elec,
+                                         const double *__restrict__ prev, const FermiState *st, double *s_tot,
+                                         FermiState *s_st)
 {
     if (pass == 0) {
         const double L = partials_combine(prev, n_bracket, 2, 0, 1, s_tot);
         const double H = partials_combine(prev, n_bracket, 2, 1, 2, s_tot);
-        if (threadIdx.x == 0) *s_st = FermiState{L, H, 0.0, 0.0};
+        if (threadIdx.x == 0) *s_st = FermiState{L, H, 0.0, 2.0 * n_rows, 0.0, 0.0, 0.0, 0.0};
     } else {
         const FermiState was = st[pass - 1];
         if (was.done != 0.0) return was;                     // the same in every thread
-        tree_totals<LEVELS>(n_rb, prev, s_tot);
-        if (threadIdx.x == 0) *s_st = tree_descend(was, LEVELS, n_elec, s_tot);
+        node_totals((unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS), prev, s_tot);
+        if (threadIdx.x == 0) *s_st = fermi_advance(was, pass - 1, n_rows, n_elec, s_tot, s_tot + 64);
     }
     __syncthreads();
     return *s_st;
@@ -710,24 +765,18 @@ __device__ inline FermiState tree_state(int pass, unsigned n_rb, unsigned n_brac
 //    every few terms), as the terms w_k = (g_(k-2) - g_k) / k;
 //  * the block's threads are 32 rows x 8 groups of nodes, so a wave reads each term
 //    once per row from LDS, without conflicts;
-//  * up to FT_DEEP rows a pass takes eight halvings (255 nodes, on eight times the
-//    blocks), as fewer rows leave the chip idle at the 15 nodes of four;
 //  * FUSED: the block first replays the previous pass's decisions itself, from its
 //    partials, where those are few enough for every block to read; otherwise
 //    k_fermi_pick does so in a launch between the passes.  (A last block that
 //    did it at the end of the pass would need a device-scope fence in every block,
 //    which writes back L2.)
-// A whole search of 640 rows, 200 terms: 16 passes of 29 us and 16 decisions of 5 -> 8
-// passes of 16; 5120 rows: the same -> 16 passes of 12; 40,960 rows: 16 of 42 + 5 -> 16
-// of 26 + 7 (an empty launch shows 4.5).
-template <int LEVELS, bool FUSED>
+template <bool FUSED>
 __global__ void __launch_bounds__(DT)
 k_fermi_pass(int n_rows, int n_exp, int pass, unsigned n_bracket, double n_elec, const double *__restrict__ gs,
              const double *__restrict__ a_inf, const double *__restrict__ b_inf, const double *__restrict__ prev,
              double *__restrict__ part, FermiState *st)
 {
-    constexpr int NODES = ft_nodes(LEVELS);
-    constexpr int NPT = LEVELS == 8 ? 4 : 2;                 // nodes per thread
+    constexpr int NPT = (FT_NODES + FP_GROUPS) / FP_GROUPS;  // nodes per thread
     __shared__ double s_w[FP_CH * FP_ROWS], s_inv[FP_CH], s_part[FP_GROUPS * NPT];
     __shared__ FermiState s_st;
     const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS);
@@ -752,8 +801,8 @@ k_fermi_pass(int n_rows, int n_exp, int pass, unsigned n_bracket, double n_elec,
     FermiState now;
     if constexpr (FUSED) {
         fetch(0);                                            // comes while the decisions are replayed
-        now = tree_state<LEVELS>(pass, n_rb, n_bracket, n_elec, prev, st, s_w, &s_st);
-        if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) st[pass] = now;
+        now = fermi_state(pass, n_rows, n_bracket, n_elec, prev, st, s_w, &s_st);
+        if (blockIdx.x == 0 && threadIdx.x == 0) st[pass] = now;
         if (now.done != 0.0) return;
     } else {
         now = *st;
@@ -761,14 +810,14 @@ k_fermi_pass(int n_rows, int n_exp, int pass, unsigned n_bracket, double n_elec,
         fetch(0);
     }
     const double ai = a_inf[r], bi = b_inf[r], g0 = gs[r];
-    // the group's nodes; those past the tree repeat its last one and are not kept
-    const int p0 = ((int)blockIdx.y * FP_GROUPS + grp) * NPT;
+    // the group's nodes; those past the last repeat it and are not kept
+    const int p0 = grp * NPT;
     // sum_k w_k sin(k theta) = sin(theta) sum_k w_k U_(k-1)(cos theta), by
     // Clenshaw's recurrence from the highest term down
     double twoc[NPT], b1[NPT], b2[NPT];
 #pragma unroll
     for (int j = 0; j < NPT; ++j) {
-        const double eps = (tree_mid(now.lo, now.hi, min(p0 + j, NODES - 1) + 1) - ai) / (2.0 * bi);
+        const double eps = (node_energy(now, pass, min(p0 + j, FT_NODES - 1)) - ai) / (2.0 * bi);
         twoc[j] = 2.0 * (eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps));
         b1[j] = 0.0;
         b2[j] = 0.0;
@@ -806,23 +855,22 @@ k_fermi_pass(int n_rows, int n_exp, int pass, unsigned n_bracket, double n_elec,
         if (row == 0) s_part[grp * NPT + j] = v;
     }
     __syncthreads();
-    const int p = (int)blockIdx.y * FP_GROUPS * NPT + threadIdx.x;
-    if (threadIdx.x < FP_GROUPS * NPT && p < NODES) part[ft_at<LEVELS>(ft_pitch(n_rb), blockIdx.x, p)] = s_part[threadIdx.x];
+    if (threadIdx.x < FT_NODES) part[threadIdx.x * ft_pitch(n_rb) + blockIdx.x] = s_part[threadIdx.x];
 }
 
 // The pass over so many rows that the chip is full: two lanes share an orbital row,
 // lane h of the pair taking nodes 8h .. 8h+7 (the last lane 7 nodes), both reading
 // the same coefficients as they go; no LDS copy and an eighth of the waves' starts
 // and ends per row.  Partials of 128 rows.
-constexpr int FT_LEVELS = 4, FT_NODES = ft_nodes(FT_LEVELS), FT_HALF = (FT_NODES + 1) / 2;
+constexpr int FT_HALF = (FT_NODES + 1) / 2;
 
 __global__ void __launch_bounds__(DT)
-k_fermi_tree(int n_rows, int n_exp, const double *__restrict__ gs, const double *__restrict__ a_inf,
+k_fermi_tree(int n_rows, int n_exp, int pass, const double *__restrict__ gs, const double *__restrict__ a_inf,
              const double *__restrict__ b_inf, double *__restrict__ part, const FermiState *st)
 {
     __shared__ double s_inv[1040], s_red[FT_NODES * (DT / 64)];
     if (st->done != 0.0) return;
-    const double lo = st->lo, hi = st->hi;
+    const FermiState now = *st;
     for (int k = threadIdx.x; k <= n_exp + 2; k += blockDim.x) s_inv[k] = k ? 1.0 / k : 0.0;
     __syncthreads();
     const long gt = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -838,7 +886,7 @@ k_fermi_tree(int n_rows, int n_exp, const double *__restrict__ gs, const double 
 #pragma unroll
             for (int j = 0; j < FT_HALF; ++j) {
                 const int p = h * FT_HALF + j < FT_NODES ? h * FT_HALF + j : FT_NODES - 1;
-                double eps = (tree_mid(lo, hi, p + 1) - ai) / (2.0 * bi);
+                double eps = (node_energy(now, pass, p) - ai) / (2.0 * bi);
                 twoc[j] = 2.0 * (eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps));
                 b1[j] = 0.0;
                 b2[j] = 0.0;
@@ -877,7 +925,7 @@ k_fermi_tree(int n_rows, int n_exp, const double *__restrict__ gs, const double 
 #pragma unroll
         for (int p = 0; p < FT_NODES; ++p) v[p] = (h == p / FT_HALF) ? cnt[p % FT_HALF] : 0.0;
         const double t = block_sum_n<FT_NODES>(v, s_red);
-        if (threadIdx.x < FT_NODES) part[ft_at<FT_LEVELS>(gridDim.x, blockIdx.x, threadIdx.x)] = t;
+        if (threadIdx.x < FT_NODES) part[threadIdx.x * (size_t)gridDim.x + blockIdx.x] = t;
     }
 }
 
@@ -890,10 +938,10 @@ constexpr int FT_PICK = 4;
 
 template <int Q>
 __global__ void __launch_bounds__(FT_PICK * DT)
-k_fermi_pick(unsigned n_rb, double n_elec, const double *__restrict__ part, FermiState *st)
+k_fermi_pick(unsigned n_rb, int pass, int n_rows, double n_elec, const double *__restrict__ part, FermiState *st)
 {
     constexpr int NPT = (FT_NODES + FT_PICK - 1) / FT_PICK, NW = DT / 64, AHEAD = 8 / Q;
-    __shared__ double s_red[FT_PICK][NPT * NW], s_tot[FT_PICK * NPT];
+    __shared__ double s_red[FT_PICK][NPT * NW], s_tot[FT_PICK * NPT], s_v[FT_NODES + 2];
     if (st->done != 0.0) return;
     const unsigned t = threadIdx.x % DT, set = threadIdx.x / DT, n = (n_rb + Q - 1) / Q;
     const size_t pitch = Q == 1 ? n_rb : ft_pitch(n_rb);
@@ -908,8 +956,7 @@ k_fermi_pick(unsigned n_rb, double n_elec, const double *__restrict__ part, Ferm
             for (int p = 0; p < NPT; ++p)
 #pragma unroll
                 for (unsigned e = 0; e < Q; ++e)
-                    x[i][p][e] = part[ft_at<FT_LEVELS>(pitch, min(Q * (q0 + i * DT) + e, n_rb - 1),
-                                                       min((int)set * NPT + p, FT_NODES - 1))];
+                    x[i][p][e] = part[min((int)set * NPT + p, FT_NODES - 1) * pitch + min(Q * (q0 + i * DT) + e, n_rb - 1)];
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i)
 #pragma unroll
@@ -934,66 +981,103 @@ k_fermi_pick(unsigned n_rb, double n_elec, const double *__restrict__ part, Ferm
         s_tot[set * NPT + t] = v;
     }
     __syncthreads();
-    if (threadIdx.x == 0) *st = tree_descend(*st, FT_LEVELS, n_elec, s_tot);
+    if (threadIdx.x == 0) *st = fermi_advance(*st, pass, n_rows, n_elec, s_tot, s_v);
 }
 
-__global__ void k_fermi_finish(const FermiState *st, double *E_F)
-{
-    E_F[0] = 0.5 * (st->lo + st->hi);
-}
-
-// the last pass's decisions and the level (one block)
-template <int LEVELS>
+// The end of the search, by one block: the last pass's decisions (prev: its partials; NULL
+// where they are made), for few rows the bisection that is left, should the closing passes
+// not have closed the bracket, and the level.
 __global__ void __launch_bounds__(DT)
-k_fermi_finish_fused(unsigned n_rb, double n_elec, int pass, const double *__restrict__ prev, const FermiState *st,
-                     double *E_F)
+k_fermi_finish(int n_rows, int n_exp, int pass, double n_elec, const double *__restrict__ gs,
+               const double *__restrict__ a_inf, const double *__restrict__ b_inf, const double *__restrict__ prev,
+               const FermiState *st, double *E_F)
 {
-    __shared__ double s_tot[256];
+    __shared__ double s_tot[96], s_red[FT_NODES * (DT / 64)];
     __shared__ FermiState s_st;
-    const FermiState now = tree_state<LEVELS>(pass, n_rb, 0, n_elec, prev, st, s_tot, &s_st);
-    if (threadIdx.x == 0) E_F[0] = 0.5 * (now.lo + now.hi);
-}
-
-// The search over n_rows rows, where each block replays the previous decisions.
-// `tree` holds the partials of two passes in turn and the states of all; NULL where the
-// caller's workspace has no room for it.
-template <int LEVELS>
-static void fermi_search_fused(int n_rows, int n_exp, double n_elec, const double *gs, const double *a_inf,
-                               const double *b_inf, unsigned n_bracket, const double *bracket, double *tree,
-                               FermiState *st, double *E_F, hipStream_t stream)
-{
-    constexpr int NPT = LEVELS == 8 ? 4 : 2, PER_Y = FP_GROUPS * NPT, PASSES = (FT_MAX_HALVINGS + LEVELS - 1) / LEVELS;
-    const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS);
-    const dim3 grid(n_rb, (ft_nodes(LEVELS) + PER_Y - 1) / PER_Y);
-    double *buf[2] = {tree, tree + ft_pitch(n_rb) * (ft_nodes(LEVELS) + 1)};
-    for (int it = 0; it < PASSES; ++it)
-        k_fermi_pass<LEVELS, true><<<grid, DT, 0, stream>>>(n_rows, n_exp, it, n_bracket, n_elec, gs, a_inf, b_inf,
-                                                               it ? buf[(it - 1) & 1] : bracket, buf[it & 1], st);
-    k_fermi_finish_fused<LEVELS><<<1, DT, 0, stream>>>(n_rb, n_elec, PASSES, buf[(PASSES - 1) & 1], st, E_F);
-}
-
-static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs, const double *a_inf,
-                         const double *b_inf, unsigned n_bracket, double *part, double *tree, FermiState *st,
-                         double *E_F, hipStream_t stream)
-{
-    const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS), n_tb = (unsigned)((2L * n_rows + DT - 1) / DT);
-    k_bracket_pick<<<1, DT, 0, stream>>>(n_bracket, part, st);
-    for (int it = 0; it < FT_MAX_HALVINGS / FT_LEVELS; ++it) {
-        if (tree) {
-            k_fermi_pass<FT_LEVELS, false><<<n_rb, DT, 0, stream>>>(n_rows, n_exp, it, 0, n_elec, gs, a_inf, b_inf,
-                                                                    nullptr, tree, st);
-            k_fermi_pick<4><<<1, FT_PICK * DT, 0, stream>>>(n_rb, n_elec, tree, st);
-        } else {
-            k_fermi_tree<<<n_tb, DT, 0, stream>>>(n_rows, n_exp, gs, a_inf, b_inf, part, st);
-            k_fermi_pick<1><<<1, FT_PICK * DT, 0, stream>>>(n_tb, n_elec, part, st);
+    FermiState now = prev ? fermi_state(pass, n_rows, 0, n_elec, prev, st, s_tot, &s_st) : *st;
+    // at most FT_MAX_HALVINGS / FT_LEVELS rounds, the last of which sets done
+    for (int round = 0; now.done == 0.0 && round <= FT_MAX_HALVINGS / FT_LEVELS; ++round) {
+        double cnt[FT_NODES];
+#pragma unroll
+        for (int p = 0; p < FT_NODES; ++p) cnt[p] = 0.0;
+        for (int r = threadIdx.x; r < n_rows; r += DT) {
+            const double ai = a_inf[r], bi = b_inf[r], g0 = gs[r];
+            double twoc[FT_NODES], b1[FT_NODES], b2[FT_NODES];
+#pragma unroll
+            for (int p = 0; p < FT_NODES; ++p) {
+                const double eps = (node_energy(now, pass, p) - ai) / (2.0 * bi);
+                twoc[p] = 2.0 * (eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps));
+                b1[p] = 0.0;
+                b2[p] = 0.0;
+            }
+            for (int k = n_exp + 2; k >= 1; --k) {
+                const double gl = k >= 2 ? gs[(long)(k - 2) * n_rows + r] : 0.0;
+                const double gh = k <= n_exp ? gs[(long)k * n_rows + r] : 0.0;
+                const double wk = (gl - gh) * (1.0 / k);
+#pragma unroll
+                for (int p = 0; p < FT_NODES; ++p) {
+                    const double bn = fma(twoc[p], b1[p], wk - b2[p]);
+                    b2[p] = b1[p];
+                    b1[p] = bn;
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < FT_NODES; ++p) {
+                const double c = 0.5 * twoc[p];
+                cnt[p] += g0 * (1.0 - acos(c) / M_PI) + sqrt(fmax(0.0, 1.0 - c * c)) * b1[p] / M_PI;
+            }
         }
+        const double t = block_sum_n<FT_NODES>(cnt, s_red);
+        if (threadIdx.x < FT_NODES) s_tot[threadIdx.x] = t;
+        __syncthreads();
+        if (threadIdx.x == 0) s_st = fermi_advance(now, pass, n_rows, n_elec, s_tot, s_tot + 64);
+        __syncthreads();
+        now = s_st;
     }
-    k_fermi_finish<<<1, 1, 0, stream>>>(st, E_F);
+    if (threadIdx.x == 0) E_F[0] = 0.5 * (now.lo + now.hi);
 }
 
 // Rows up to which k_fermi_pass makes the search's passes, k_fermi_tree beyond: 26 us
 // against 42 at 40,960 rows, 101 against 76 at 138,240.
 constexpr long FT_SPREAD = 65536;
+// Rows up to which the bisection left over is k_fermi_finish's one block's (80 us per
+// four halvings at the line; the launches of FT_REST passes that find nothing to do would
+// cost 50), passes of the whole grid beyond.
+constexpr long FT_FINISH = 2048;
+constexpr int FT_REST = 11;
+
+// The search.  Up to FT_FUSED rows, two trees of sums per node, each block replays the
+// previous decisions and `states` holds every pass's state.  `tree` holds the 32-row
+// partials of two passes in turn; NULL for more than FT_SPREAD rows and where the
+// caller's workspace has no room for it.
+static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs, const double *a_inf,
+                         const double *b_inf, unsigned n_bracket, double *part, double *tree, FermiState *st,
+                         FermiState *states, double *E_F, hipStream_t stream)
+{
+    const int passes = FT_TREE + FT_CLOSE + (n_rows <= FT_FINISH ? 0 : FT_REST);
+    const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS), n_tb = (unsigned)((2L * n_rows + DT - 1) / DT);
+    if (tree && n_rows <= FT_FUSED) {
+        double *buf[2] = {tree, tree + ft_pitch(n_rb) * (FT_NODES + 1)};
+        for (int it = 0; it < passes; ++it)
+            k_fermi_pass<true><<<n_rb, DT, 0, stream>>>(n_rows, n_exp, it, n_bracket, n_elec, gs, a_inf, b_inf,
+                                                        it ? buf[(it - 1) & 1] : part, buf[it & 1], states);
+        k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, n_exp, passes, n_elec, gs, a_inf, b_inf, buf[(passes - 1) & 1], states,
+                                             E_F);
+        return;
+    }
+    k_bracket_pick<<<1, DT, 0, stream>>>(n_rows, n_bracket, part, st);
+    for (int it = 0; it < passes; ++it) {
+        if (tree) {
+            k_fermi_pass<false><<<n_rb, DT, 0, stream>>>(n_rows, n_exp, it, 0, n_elec, gs, a_inf, b_inf, nullptr, tree,
+                                                         st);
+            k_fermi_pick<4><<<1, FT_PICK * DT, 0, stream>>>(n_rb, it, n_rows, n_elec, tree, st);
+        } else {
+            k_fermi_tree<<<n_tb, DT, 0, stream>>>(n_rows, n_exp, it, gs, a_inf, b_inf, part, st);
+            k_fermi_pick<1><<<1, FT_PICK * DT, 0, stream>>>(n_tb, it, n_rows, n_elec, part, st);
+        }
+    }
+    k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, n_exp, passes, n_elec, gs, a_inf, b_inf, nullptr, st, E_F);
+}
 
 // per-atom N, U, n(E_F) and block partials of U.  A row's sums over its 200 or so
 // terms are split over EN_SEGS threads, each starting its run of terms from its own
@@ -1149,8 +1233,8 @@ EnergyWs carve(void *base, long n_rows, int n_exp)
     w.bytes = (size_t)(p - (char *)base);
     if (n_rows <= FT_SPREAD) {
         const size_t rb = ft_pitch((unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS));
-        w.tree = (double *)take(sizeof(double) * 2 * rb * (n_rows <= FT_DEEP ? 256 : 16));
-        w.states = (FermiState *)take(sizeof(FermiState) * (FT_MAX_HALVINGS + 1));
+        w.tree = (double *)take(sizeof(double) * 2 * rb * (FT_NODES + 1));
+        w.states = (FermiState *)take(sizeof(FermiState) * (FT_TREE + FT_CLOSE + FT_REST));
     }
     w.bytes_tree = (size_t)(p - (char *)base);
     return w;
@@ -1225,12 +1309,8 @@ static int energy_impl(int n_atoms, int no, int n_max, int n_exp, const double *
         // for, or the fixed array at its limit) takes the route of many rows
         const double ne = n_elec / wt;
         const bool tree = R <= FT_SPREAD && ws_bytes >= w.bytes_tree;
-        if (tree && R <= FT_DEEP)
-            fermi_search_fused<8>((int)R, n_exp, ne, w.gs, a_inf, b_inf, nblk, w.part, w.tree, w.states, E_F, stream);
-        else if (tree && R <= FT_FUSED)
-            fermi_search_fused<4>((int)R, n_exp, ne, w.gs, a_inf, b_inf, nblk, w.part, w.tree, w.states, E_F, stream);
-        else
-            fermi_search((int)R, n_exp, ne, w.gs, a_inf, b_inf, nblk, w.part, tree ? w.tree : nullptr, w.st, E_F, stream);
+        fermi_search((int)R, n_exp, ne, w.gs, a_inf, b_inf, nblk, w.part, tree ? w.tree : nullptr, w.st, w.states, E_F,
+                     stream);
         BOP_LAUNCHED();
     }
     const unsigned ablk = (unsigned)((n_atoms + en_atoms(no) - 1) / en_atoms(no));

@@ -81,3 +81,25 @@ def test_level_without_search_workspace(bop, n_atoms, no, n_exp):
         assert np.array_equal(full[k].view(np.int64), small[k].view(np.int64)), k
     with pytest.raises(bop.BopError):
         _gpu(bop, mu, rec, on, n_elec, 8, n_exp, ws=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("R", [40, 3000, 17000, 65700])
+@pytest.mark.parametrize("fill", [0.0, 1e-7, 0.3, 0.5, 0.5 + 1e-4, 0.75, 1.0 - 1e-6, 1.0])
+def test_level_with_gap_and_band_edges(bop, R, fill):
+    """Two sets of rows with bands about [-4, -2] and [2, 4], each row's ending at energies
+    of its own: levels inside a band, at band edges, in the gap, and with no
+    and all electrons, where the search bisects on, by each of its routes."""
+    n_exp, half = 20, R // 2
+    mu, rec, on = _rows(R, 1, 5, seed=9)
+    a, b = 0.2 * rec["a"], 0.2 * rec["b"]
+    shift = np.where(np.arange(R) < half, -3.0, 3.0)
+    rec = {"a": a + shift[:, None], "b": b, "a_inf": shift, "b_inf": np.full(R, 0.5) * np.linspace(0.99, 1.01, R),
+           "flags": np.zeros(R, np.int32)}
+    gs, chain = O.dos_coeffs(mu, rec, 5, n_exp, with_chain=True)
+    gs[:, :6] = O.jackson(n_exp)[:6] * chain
+    n_elec = 2.0 * (half * min(2 * fill, 1.0) + (R - half) * max(2 * fill - 1.0, 0.0))
+    E = float(_gpu(bop, None, rec, on, n_elec, 5, n_exp)["E_F"][0])
+    # half units of the counts' terms, and of the level over their slope: 1e-12 per row
+    assert abs(O.count(gs, rec["a_inf"], rec["b_inf"], E) - n_elec) <= 1e-11 * R
+    lo, hi = (shift - 2 * rec["b_inf"]).min(), (shift + 2 * rec["b_inf"]).max()
+    assert lo <= E <= hi
