@@ -22,6 +22,7 @@
 // one-block launch that follows, so results are deterministic and no block
 // needs a device-scope fence (which would write back L2).
 #include "bop_internal.h"
+#include "series.h"
 
 #include <cmath>
 #include <mutex>
@@ -260,24 +261,6 @@ k_recursion_reg(int n_rows, int n_max, const double *__restrict__ mu, int bw_mod
 // ---------------------------------------------------------------------------
 // expansion coefficients g_m sigma_m, m-major
 // ---------------------------------------------------------------------------
-// Jackson kernel of length n_exp adapted to U polynomials: g_m = g^J_(m+1)/g^J_1
-// (whole block)
-__device__ inline void jackson_table(int n_exp, double *s_g)
-{
-    const double w = M_PI / (n_exp + 1.0);
-    double sw, cw;
-    sincos(w, &sw, &cw);
-    const double cotw = cw / sw;
-    const double g1 = ((double)n_exp * cw + sw * cotw) / (n_exp + 1.0);
-    for (int m = threadIdx.x; m <= n_exp; m += blockDim.x) {
-        int mm = m + 1;
-        double sm, cm;
-        sincos(w * mm, &sm, &cm);
-        double gj = ((double)(n_exp - mm + 1) * cm + sm * cotw) / (n_exp + 1.0);
-        s_g[m] = gj / g1;
-    }
-}
-
 template <int LM>
 __global__ void __launch_bounds__(DT)
 k_dos_coeffs(int n_rows, int n_max, int n_exp, const double *__restrict__ mu,
@@ -289,18 +272,7 @@ k_dos_coeffs(int n_rows, int n_max, int n_exp, const double *__restrict__ mu,
     __shared__ double s_c[(MAX_NMAX + 1) * (MAX_NMAX + 1)];   // binomials
     __shared__ double s_g[1025];                              // Jackson g_m
     const int M = n_max + 1;
-    if (threadIdx.x == 0) {
-        for (int t = 0; t < M * M; ++t) { s_p[t] = 0.0; s_c[t] = 0.0; }
-        s_p[0] = 1.0;
-        if (M > 1) s_p[M + 1] = 2.0;
-        for (int m = 1; m + 1 < M; ++m)
-            for (int n = 0; n <= m + 1; ++n)
-                s_p[(m + 1) * M + n] = (n >= 1 ? 2.0 * s_p[m * M + n - 1] : 0.0) - (n <= m - 1 ? s_p[(m - 1) * M + n] : 0.0);
-        for (int n = 0; n < M; ++n) {
-            s_c[n * M] = 1.0;
-            for (int l = 1; l <= n; ++l) s_c[n * M + l] = s_c[(n - 1) * M + l - 1] + (l <= n - 1 ? s_c[(n - 1) * M + l] : 0.0);
-        }
-    }
+    series_tables(M, s_p, s_c);
     jackson_table(n_exp, s_g);
     __syncthreads();
     int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -415,24 +387,7 @@ k_dos_coeffs_lanes(int n_rows, int n_max, int n_exp, const double *__restrict__ 
         const double *mr = mu + rr * M;
         const double m0 = mr[0];
         for (int n = k; n < M; n += CL) s_m[row][n] = mr[n] / m0;
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        if (wave == 0) {                                      // column l = lane of Pascal's triangle
-            double c = lane == 0 ? 1.0 : 0.0;
-            for (int n = 0; n < M; ++n) {
-                if (lane < M) s_c[n * M + lane] = c;
-                const double below = __shfl_up(c, 1);
-                c += lane > 0 ? below : 0.0;
-            }
-        } else if (wave == 1) {                               // column n = lane of the U polynomials
-            double p0 = 0.0, p1 = lane == 0 ? 1.0 : 0.0;
-            for (int m = 0; m < M; ++m) {
-                if (lane < M) s_p[m * M + lane] = p1;
-                const double below = __shfl_up(p1, 1);
-                const double p2 = (lane > 0 ? 2.0 * below : 0.0) - p0;
-                p0 = p1;
-                p1 = p2;
-            }
-        }
+        series_tables(M, s_p, s_c);
     }
     jackson_table(n_exp, s_g);
     __syncthreads();

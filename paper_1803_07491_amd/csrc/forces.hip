@@ -48,6 +48,7 @@
 //    sum_ab Theta~_p,ab dH_p,ab/dd_p (d_p = r_j + S - r_i); with the doubled
 //    canonical direction and a zero reverse this is the same sum.
 #include "bop_internal.h"
+#include "series.h"
 #include "tiles.h"
 
 #include <cmath>
@@ -171,41 +172,27 @@ __device__ inline int fb_of(int n_max) { return n_max / 2; }
 // branch decisions (breakdown, band edges, width floor, inside the band) are
 // taken on the values.  Writes dU, dN [R][n_max + 1] (column 0 untouched) and,
 // from the dir = 1 thread, n_r(E_F) of the row.
-// Two waves per SIMD: unbounded, the compiler takes all 256 VGPRs and runs
-// one; bounded to four it spills the chain.
-template <int LM>
-__global__ void __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(2, 8)))
+// For n_max <= NM, every loop over moments and levels unrolled, so that no array is
+// indexed at run time: arrays in scratch memory took most of the time.  Unrolled, with
+// the tables built by a lane per column, same bits: 250 atoms at 10 moments 272 -> 143 us,
+// at 18 490 -> 233; 11,664 atoms at 18 6.90 -> 2.75 ms, at 10 1.90 -> 1.01.  Two waves
+// per SIMD, with spills at 18 (one: 211 us and 3.06 ms); one at 20, where two spill
+// most of the recursion (240 against 385 us, 128 atoms).
+template <int NM>
+__global__ void __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(NM <= 18 ? 2 : 1, 8)))
 k_weights(int R, int n_max, int n_exp, const double *__restrict__ mu, const double *__restrict__ H_on,
           const double *__restrict__ E_F, double *__restrict__ dU, double *__restrict__ dN, double *__restrict__ Drow)
 {
     using D1 = Dual<1>;
-    __shared__ double s_p[(F_MAXN + 1) * (F_MAXN + 1)];   // coefficients of U_m in powers of x
-    __shared__ double s_c[(F_MAXN + 1) * (F_MAXN + 1)];   // binomials
+    constexpr int LM = NM / 2, NA = (NM - 1) / 2 + 1, NB = NM / 2;
+    __shared__ double s_p[(NM + 1) * (NM + 1)];           // coefficients of U_m in powers of x
+    __shared__ double s_c[(NM + 1) * (NM + 1)];           // binomials
     __shared__ double s_g[1025];                          // Jackson factors for U_m
     __shared__ double s_inv[1030];
     const int M = n_max + 1;
-    if (threadIdx.x == 0) {
-        for (int t = 0; t < M * M; ++t) { s_p[t] = 0.0; s_c[t] = 0.0; }
-        s_p[0] = 1.0;
-        if (M > 1) s_p[M + 1] = 2.0;
-        for (int m = 1; m + 1 < M; ++m)
-            for (int q = 0; q <= m + 1; ++q)
-                s_p[(m + 1) * M + q] = (q >= 1 ? 2.0 * s_p[m * M + q - 1] : 0.0) - (q <= m - 1 ? s_p[(m - 1) * M + q] : 0.0);
-        for (int q = 0; q < M; ++q) {
-            s_c[q * M] = 1.0;
-            for (int l = 1; l <= q; ++l) s_c[q * M + l] = s_c[(q - 1) * M + l - 1] + (l <= q - 1 ? s_c[(q - 1) * M + l] : 0.0);
-        }
-    }
-    {
-        const double wj = M_PI / (n_exp + 1.0);
-        const double cotw = cos(wj) / sin(wj);
-        const double g1 = ((double)n_exp * cos(wj) + sin(wj) * cotw) / (n_exp + 1.0);
-        for (int m = threadIdx.x; m <= n_exp; m += blockDim.x) {
-            const int mm = m + 1;
-            s_g[m] = (((double)(n_exp - mm + 1) * cos(wj * mm) + sin(wj * mm) * cotw) / (n_exp + 1.0)) / g1;
-        }
-        for (int k = threadIdx.x; k <= n_exp + 4; k += blockDim.x) s_inv[k] = k ? 1.0 / k : 0.0;
-    }
+    series_tables(M, s_p, s_c);
+    jackson_table(n_exp, s_g);
+    for (int k = threadIdx.x; k <= n_exp + 4; k += blockDim.x) s_inv[k] = k ? 1.0 / k : 0.0;
     __syncthreads();
     const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const long r = tid / n_max;
@@ -214,46 +201,63 @@ k_weights(int R, int n_max, int n_exp, const double *__restrict__ mu, const doub
     const int na = fa_of(n_max), nb = fb_of(n_max);
     const double *mr = mu + r * M;
     const double m0 = mr[0];
-    D1 m[F_MAXN + 1];
-    for (int t = 0; t < M; ++t) {
-        m[t] = dc<1>(mr[t] / m0);
+    D1 m[NM + 1];
+#pragma unroll
+    for (int t = 0; t <= NM; ++t) {
+        m[t] = dc<1>(t < M ? mr[t] / m0 : 0.0);
         m[t].d[0] = (t == dir) ? 1.0 / m0 : 0.0;
     }
     // recursion coefficients from the moments (orthonormal polynomials by
     // their coefficients in powers of H)
-    D1 a[F_MAXN / 2 + 1], b[F_MAXN / 2 + 2];
-    D1 cp[F_MAXN / 2 + 3], cc[F_MAXN / 2 + 3], dv[F_MAXN / 2 + 3];
-    for (int q = 0; q < F_MAXN / 2 + 3; ++q) { cp[q] = dc<1>(0.0); cc[q] = dc<1>(0.0); }
-    for (int q = 0; q < F_MAXN / 2 + 2; ++q) b[q] = dc<1>(0.0);
+    D1 a[NA], b[NB + 1];
+    {
+    D1 cp[NB + 2], cc[NB + 2], dv[NB + 2];
+#pragma unroll
+    for (int q = 0; q < NB + 2; ++q) { cp[q] = dc<1>(0.0); cc[q] = dc<1>(0.0); dv[q] = dc<1>(0.0); }
+#pragma unroll
+    for (int q = 0; q <= NB; ++q) b[q] = dc<1>(0.0);
     cc[0] = dc<1>(1.0);
     D1 bn = dc<1>(0.0);
     const double var = n_max >= 2 ? m[2].v - m[1].v * m[1].v : 0.0;
-    bool broke = false;
-    for (int q = 0; q < na; ++q) {
-        if (broke) { a[q] = a[q - 1]; continue; }
+    bool broke = false, ended = false;
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+        a[q] = dc<1>(0.0);
+        if (q >= na || ended) continue;
+        if (broke) { a[q] = a[q > 0 ? q - 1 : 0]; continue; }
         D1 s = dc<1>(0.0);
+#pragma unroll
         for (int j = 0; j <= q; ++j)
+#pragma unroll
             for (int l = 0; l <= q; ++l) s = s + cc[j] * cc[l] * m[j + l + 1];
         a[q] = s;
-        if (q + 1 > nb) break;
-        for (int j = 0; j <= q + 1; ++j) dv[j] = (j > 0 ? cc[j - 1] : dc<1>(0.0)) - s * cc[j] - bn * cp[j];
+        if (q + 1 > nb) { ended = true; continue; }
+#pragma unroll
+        for (int j = 0; j <= q + 1; ++j) dv[j] = (j > 0 ? cc[j > 0 ? j - 1 : 0] : dc<1>(0.0)) - s * cc[j] - bn * cp[j];
         D1 b2 = dc<1>(0.0);
+#pragma unroll
         for (int j = 0; j <= q + 1; ++j)
-            for (int l = 0; l <= q + 1; ++l) b2 = b2 + dv[j] * dv[l] * m[j + l];
+#pragma unroll
+            for (int l = 0; l <= q + 1; ++l)
+                if (j + l <= NM) b2 = b2 + dv[j] * dv[l] * m[j + l];
         if (!(b2.v > 1e-14 * var)) {
             broke = true;
             continue;
         }
         const D1 bb = dsqrt(b2);
-        b[q + 1] = bb;
+        if (q + 1 <= NB) b[q + 1] = bb;
+#pragma unroll
         for (int j = 0; j <= q + 1; ++j) { cp[j] = cc[j]; cc[j] = dv[j] / bb; }
         bn = bb;
     }
+    }
     // Gershgorin band edges (the extremes chosen by value)
     D1 lo = dc<1>(0.0), hi = dc<1>(0.0);
-    for (int q = 0; q < na; ++q) {
-        const D1 bl = (q >= 1 && q <= nb) ? b[q] : dc<1>(0.0);
-        const D1 bh = (q + 1 <= nb) ? b[q + 1] : dc<1>(0.0);
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+        if (q >= na) continue;
+        const D1 bl = (q >= 1 && q <= nb) ? b[q <= NB ? q : 0] : dc<1>(0.0);
+        const D1 bh = (q + 1 <= nb) ? b[q + 1 <= NB ? q + 1 : 0] : dc<1>(0.0);
         const D1 e0 = a[q] - bl - bh, e1 = a[q] + bl + bh;
         if (q == 0 || e0.v < lo.v) lo = e0;
         if (q == 0 || e1.v > hi.v) hi = e1;
@@ -264,13 +268,19 @@ k_weights(int R, int n_max, int n_exp, const double *__restrict__ mu, const doub
     const int n_mom = bi.v > 1e-6 ? n_max : 0;
     // sigma_m from the moments for m <= n_mom: normalised moments of the
     // scaled variable, then the U_m coefficients
-    D1 gm[F_MAXN + 1];
+    D1 gm[NM + 1];
+#pragma unroll
+    for (int q = 0; q <= NM; ++q) gm[q] = dc<1>(0.0);
     if (n_mom > 0) {
-        D1 mh[F_MAXN + 1];
+        D1 mh[NM + 1];
         const D1 two_b = 2.0 * bi;
         D1 scale = dc<1>(1.0);
-        for (int q = 0; q < M; ++q) {
+#pragma unroll
+        for (int q = 0; q <= NM; ++q) {
+            mh[q] = dc<1>(0.0);
+            if (q >= M) continue;
             D1 s = dc<1>(0.0), pa = dc<1>(1.0);
+#pragma unroll
             for (int l = 0; l <= q; ++l) {
                 s = s + s_c[q * M + l] * (pa * m[q - l]);
                 pa = pa * (-ai);
@@ -278,8 +288,11 @@ k_weights(int R, int n_max, int n_exp, const double *__restrict__ mu, const doub
             mh[q] = s / scale;
             scale = scale * two_b;
         }
-        for (int q = 0; q < M; ++q) {
+#pragma unroll
+        for (int q = 0; q <= NM; ++q) {
+            if (q >= M) continue;
             D1 s = dc<1>(0.0);
+#pragma unroll
             for (int l = 0; l <= q; ++l) s = s + s_p[q * M + l] * mh[l];
             gm[q] = s;
         }
@@ -292,13 +305,13 @@ k_weights(int R, int n_max, int n_exp, const double *__restrict__ mu, const doub
     const D1 tb = 2.0 * bi;
 #pragma unroll
     for (int k = 0; k <= LM; ++k) {
-        ah[k] = (k < na) ? (a[k < na ? k : 0] - ai) / tb : dc<1>(0.0);
+        ah[k] = (k < na) ? (a[k < NA ? k : 0] - ai) / tb : dc<1>(0.0);
         z0[k] = dc<1>(0.0);
         z1[k] = dc<1>(0.0);
     }
 #pragma unroll
     for (int k = 0; k <= LM + 1; ++k)
-        bh[k] = (k == 0) ? dc<1>(0.0) : ((k <= nb) ? b[k <= nb ? k : 0] / tb : dc<1>(0.5));
+        bh[k] = (k == 0) ? dc<1>(0.0) : ((k <= nb) ? b[k <= NB ? k : 0] / tb : dc<1>(0.5));
     z1[0] = dc<1>(1.0);
     // N, U and n(E) at E_F by the Chebyshev sums with chi functions, the
     // sines advanced by rotation
@@ -349,7 +362,7 @@ k_weights(int R, int n_max, int n_exp, const double *__restrict__ mu, const doub
     // m <= n_mom: sigma_m from the moments (unrolled, so that gm is indexed
     // at compile time and dies before the chain's arrays are live)
 #pragma unroll
-    for (int q = 0; q <= F_MAXN; ++q)
+    for (int q = 0; q <= NM; ++q)
         if (q <= n_mom && q <= n_exp) term(q, n_mom > 0 ? gm[q] : dc<1>(1.0));
     // m > n_mom: sigma_m from the chain, first advanced to sigma_(n_mom + 1)
     if (n_mom < n_exp) {
@@ -981,11 +994,9 @@ extern "C" int bop_weights(int n_rows, int n_max, int n_exp, const double *mu, c
     BOP_REQUIRE(ws && ws_bytes >= ww.bytes, BOP_E_CAPACITY, "bop_weights: workspace of %zu bytes needed", ww.bytes);
     const long nt = (long)n_rows * n_max;
     const unsigned g = (unsigned)((nt + WT - 1) / WT);
-    // chain depth L = max(#a, #b) = (n_max + 1) / 2 levels below the delay level
-    if ((n_max + 1) / 2 <= 9)
-        k_weights<9><<<g, WT, 0, stream>>>(n_rows, n_max, n_exp, mu, H_on, E_F, w, ww.dN, ww.Drow);
-    else
-        k_weights<11><<<g, WT, 0, stream>>>(n_rows, n_max, n_exp, mu, H_on, E_F, w, ww.dN, ww.Drow);
+    if (n_max <= 10) k_weights<10><<<g, WT, 0, stream>>>(n_rows, n_max, n_exp, mu, H_on, E_F, w, ww.dN, ww.Drow);
+    else if (n_max <= 18) k_weights<18><<<g, WT, 0, stream>>>(n_rows, n_max, n_exp, mu, H_on, E_F, w, ww.dN, ww.Drow);
+    else k_weights<F_MAXN><<<g, WT, 0, stream>>>(n_rows, n_max, n_exp, mu, H_on, E_F, w, ww.dN, ww.Drow);
     BOP_LAUNCHED();
     const unsigned rb = (unsigned)((n_rows + WT - 1) / WT);
     k_ebar_part<<<rb, WT, 0, stream>>>(n_rows, H_on, ww.Drow, ww.part);

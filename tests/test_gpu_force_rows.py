@@ -30,3 +30,30 @@ def test_forces_by_row_length(bop, reps, cut, deg, n_max):
         p, _, F = _gpu_forces(bop, wl, dtype)
         assert p.plan.deg_max == deg
         assert np.abs(F - ref).max() <= tol * scale, dtype
+
+
+@pytest.mark.parametrize("n_max", [10, 11, 18, 19, 20])
+def test_weights_by_moment_count(bop, n_max):
+    """Weights at the moment counts that end the kernel's forms."""
+    import torch
+    pos, cell = W.cubic_lattice("bcc", 2.87, 3)
+    pos = W.displace(pos, cell, 0.05, W._rng(5))
+    n = len(pos)
+    wl = W.Workload("w", pos, cell, np.zeros(n, np.int32), W.canonical_d_model(3.5), n_max, 200, np.full(n, 6.5))
+    nl = O.neighbours(pos, cell, wl.model["r_cut"])
+    H_on, H = O.build_H(wl.model, wl.species, nl)
+    mu = O.moments(nl, H_on, H, n_max).reshape(-1, n_max + 1)[:10]
+    on = np.asarray(H_on)[:2]
+    E = 0.07
+    ref = lambda m: O.weights(m, n_max, 200, E, on.reshape(-1))[0]  # noqa: E731
+    want = ref(mu)
+    got = bop.weights(torch.as_tensor(mu.reshape(2, 5, -1), device="cuda"), torch.as_tensor(on, device="cuda"),
+                      torch.tensor([E], dtype=torch.float64, device="cuda"), n_max).cpu().numpy()
+    # the reference's own response to a change of the moments by 1e-10 stands for its
+    # conditioning; both sides round their moments' products, some hundreds of half units
+    rng = np.random.default_rng(1)
+    moved = np.max([np.abs(ref(mu * (1 + 1e-10 * rng.choice([-1.0, 1.0], mu.shape))) - want) for _ in range(4)], axis=0)
+    tol = 1e3 * 2.0 ** -53 / 1e-10 * moved.max(0) + 1e-12 * np.abs(want).max(0)
+    ok = np.isfinite(want).all(0) & (tol < 0.1 * np.abs(want).max(0) + 1e-300)
+    assert ok[1:].any()
+    assert np.all(np.abs(got - want).max(0)[ok] <= tol[ok])
