@@ -542,8 +542,8 @@ k_bracket_pick(int n_rows, unsigned n_blocks, const double *__restrict__ part, F
 //    (a band edge in the bracket).
 // Four passes then do for what bisection alone takes 15 for.  Against it the level is
 // within 1e-15 eV over 54 to 27,648 atoms and 1 to 1024 terms; whole tails, 200 terms: 128
-// atoms 168 -> 91 us, 2000 atoms 326 -> 171, 8192 atoms 590 -> 300, 128,000 atoms 6.16 ->
-// 2.16 ms.
+// atoms 168 -> 130 us, 2000 atoms 326 -> 177, 8192 atoms 590 -> 308, 128,000 atoms 6.16 ->
+// 2.15 ms; bisected throughout (a gap) 1000 rows take 210 us.
 constexpr int FT_MAX_HALVINGS = 64;            // as many as plain bisection takes at most
 constexpr int FT_LEVELS = 4, FT_NODES = (1 << FT_LEVELS) - 1;
 constexpr int FT_TREE = 3, FT_CLOSE = 2;       // bisecting passes first, closing passes then
@@ -628,6 +628,7 @@ __device__ inline FermiState fermi_advance(const FermiState &st, int pass, int n
             else { s.hi = m; s.nhi = c; node = 2 * node; }
             s.halvings += 1.0;
         }
+        if (s.halvings >= FT_MAX_HALVINGS) s.done = 1.0;
         if (pass != FT_TREE - 1 || s.done != 0.0) return s;
         const double step = s.nhi - s.nlo, off = fmin(s.nhi - n_elec, n_elec - s.nlo);
         if (!(step >= FT_SLOPE * n_rows && off >= step / (1 << 16))) {
@@ -939,67 +940,25 @@ k_fermi_pick(unsigned n_rb, int pass, int n_rows, double n_elec, const double *_
     if (threadIdx.x == 0) *st = fermi_advance(*st, pass, n_rows, n_elec, s_tot, s_v);
 }
 
-// The end of the search, by one block: the last pass's decisions (prev: its partials; NULL
-// where they are made), for few rows the bisection that is left, should the closing passes
-// not have closed the bracket, and the level.
+// The level, by one block: where the blocks replay the decisions, after the last pass's
+// (prev: its partials; else NULL).
 __global__ void __launch_bounds__(DT)
-k_fermi_finish(int n_rows, int n_exp, int pass, double n_elec, const double *__restrict__ gs,
-               const double *__restrict__ a_inf, const double *__restrict__ b_inf, const double *__restrict__ prev,
-               const FermiState *st, double *E_F)
+k_fermi_finish(int n_rows, int pass, double n_elec, const double *__restrict__ prev, const FermiState *st, double *E_F)
 {
-    __shared__ double s_tot[96], s_red[FT_NODES * (DT / 64)];
+    __shared__ double s_tot[96];
     __shared__ FermiState s_st;
-    FermiState now = prev ? fermi_state(pass, n_rows, 0, n_elec, prev, st, s_tot, &s_st) : *st;
-    // at most FT_MAX_HALVINGS / FT_LEVELS rounds, the last of which sets done
-    for (int round = 0; now.done == 0.0 && round <= FT_MAX_HALVINGS / FT_LEVELS; ++round) {
-        double cnt[FT_NODES];
-#pragma unroll
-        for (int p = 0; p < FT_NODES; ++p) cnt[p] = 0.0;
-        for (int r = threadIdx.x; r < n_rows; r += DT) {
-            const double ai = a_inf[r], bi = b_inf[r], g0 = gs[r];
-            double twoc[FT_NODES], b1[FT_NODES], b2[FT_NODES];
-#pragma unroll
-            for (int p = 0; p < FT_NODES; ++p) {
-                const double eps = (node_energy(now, pass, p) - ai) / (2.0 * bi);
-                twoc[p] = 2.0 * (eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps));
-                b1[p] = 0.0;
-                b2[p] = 0.0;
-            }
-            for (int k = n_exp + 2; k >= 1; --k) {
-                const double gl = k >= 2 ? gs[(long)(k - 2) * n_rows + r] : 0.0;
-                const double gh = k <= n_exp ? gs[(long)k * n_rows + r] : 0.0;
-                const double wk = (gl - gh) * (1.0 / k);
-#pragma unroll
-                for (int p = 0; p < FT_NODES; ++p) {
-                    const double bn = fma(twoc[p], b1[p], wk - b2[p]);
-                    b2[p] = b1[p];
-                    b1[p] = bn;
-                }
-            }
-#pragma unroll
-            for (int p = 0; p < FT_NODES; ++p) {
-                const double c = 0.5 * twoc[p];
-                cnt[p] += g0 * (1.0 - acos(c) / M_PI) + sqrt(fmax(0.0, 1.0 - c * c)) * b1[p] / M_PI;
-            }
-        }
-        const double t = block_sum_n<FT_NODES>(cnt, s_red);
-        if (threadIdx.x < FT_NODES) s_tot[threadIdx.x] = t;
-        __syncthreads();
-        if (threadIdx.x == 0) s_st = fermi_advance(now, pass, n_rows, n_elec, s_tot, s_tot + 64);
-        __syncthreads();
-        now = s_st;
-    }
+    const FermiState now = prev ? fermi_state(pass, n_rows, 0, n_elec, prev, st, s_tot, &s_st) : *st;
     if (threadIdx.x == 0) E_F[0] = 0.5 * (now.lo + now.hi);
 }
 
 // Rows up to which k_fermi_pass makes the search's passes, k_fermi_tree beyond: 26 us
 // against 42 at 40,960 rows, 101 against 76 at 138,240.
 constexpr long FT_SPREAD = 65536;
-// Rows up to which the bisection left over is k_fermi_finish's one block's (80 us per
-// four halvings at the line; the launches of FT_REST passes that find nothing to do would
-// cost 50), passes of the whole grid beyond.
-constexpr long FT_FINISH = 2048;
-constexpr int FT_REST = 11;
+// Passes after the closing ones, which find nothing to do where those closed the bracket:
+// every halving that can be left.  (One block doing what is left instead saves their 40
+// us, but takes 1.1 ms for 1000 rows with a gap, where they take 0.2 and bisecting all the
+// way took 0.67.)
+constexpr int FT_REST = (FT_MAX_HALVINGS - FT_TREE * FT_LEVELS) / FT_LEVELS;
 
 // The search.  Up to FT_FUSED rows, two trees of sums per node, each block replays the
 // previous decisions and `states` holds every pass's state.  `tree` holds the 32-row
@@ -1009,15 +968,14 @@ static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs,
                          const double *b_inf, unsigned n_bracket, double *part, double *tree, FermiState *st,
                          FermiState *states, double *E_F, hipStream_t stream)
 {
-    const int passes = FT_TREE + FT_CLOSE + (n_rows <= FT_FINISH ? 0 : FT_REST);
+    const int passes = FT_TREE + FT_CLOSE + FT_REST;
     const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS), n_tb = (unsigned)((2L * n_rows + DT - 1) / DT);
     if (tree && n_rows <= FT_FUSED) {
         double *buf[2] = {tree, tree + ft_pitch(n_rb) * (FT_NODES + 1)};
         for (int it = 0; it < passes; ++it)
             k_fermi_pass<true><<<n_rb, DT, 0, stream>>>(n_rows, n_exp, it, n_bracket, n_elec, gs, a_inf, b_inf,
                                                         it ? buf[(it - 1) & 1] : part, buf[it & 1], states);
-        k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, n_exp, passes, n_elec, gs, a_inf, b_inf, buf[(passes - 1) & 1], states,
-                                             E_F);
+        k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, passes, n_elec, buf[(passes - 1) & 1], states, E_F);
         return;
     }
     k_bracket_pick<<<1, DT, 0, stream>>>(n_rows, n_bracket, part, st);
@@ -1031,7 +989,7 @@ static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs,
             k_fermi_pick<1><<<1, FT_PICK * DT, 0, stream>>>(n_tb, it, n_rows, n_elec, part, st);
         }
     }
-    k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, n_exp, passes, n_elec, gs, a_inf, b_inf, nullptr, st, E_F);
+    k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, passes, n_elec, nullptr, st, E_F);
 }
 
 // per-atom N, U, n(E_F) and block partials of U.  A row's sums over its 200 or so
