@@ -449,22 +449,9 @@ k_dos_coeffs_lanes(int n_rows, int n_max, int n_exp, const double *__restrict__ 
 // ---------------------------------------------------------------------------
 // per-orbital sums at energy E
 // ---------------------------------------------------------------------------
-__device__ inline double block_sum(double v, double *s_red)
-{
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) s_red[w] = v;
-    __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0)
-        for (int q = 0; q < (int)(blockDim.x >> 6); ++q) t += s_red[q];
-    __syncthreads();
-    return t;    // valid in thread 0
-}
-
 // Block sums of N values per thread at once: each wave folds its values with
 // shuffles, one barrier, then thread p < N adds the waves' values in wave
-// order (the same additions, in the same order, as N separate block_sum calls).
+// order.
 // Result valid in thread p for value p.
 template <int N>
 __device__ inline double block_sum_n(double (&v)[N], double *s_red /* N x (DT / 64) */)
@@ -1011,7 +998,7 @@ k_energy(int n_atoms, int no, int n_exp, double wt, const double *__restrict__ g
          double *__restrict__ N_atom, double *__restrict__ U_atom, double *__restrict__ dos_atom,
          int *__restrict__ flags, double *__restrict__ part)
 {
-    __shared__ double s_inv[1024 + EN_TAB], s_s[3][EN_MAXT], s_red[EN_MAXT / 64];
+    __shared__ double s_inv[1024 + EN_TAB], s_s[3][EN_MAXT];
     const int EA = en_atoms(no), RB = EA * no;
     const int row = threadIdx.x % RB, seg = threadIdx.x / RB;
     const long n_rows = (long)n_atoms * no;
@@ -1112,8 +1099,11 @@ k_energy(int n_atoms, int no, int n_exp, double wt, const double *__restrict__ g
         dos_atom[i] = 2.0 * wt * sD;
         Ui = 2.0 * wt * sU;
     }
-    const double tb = block_sum(Ui, s_red);
-    if (threadIdx.x == 0) part[blockIdx.x] = tb;
+    // the block's atoms are in its first wave (a block may end in part of a wave, so
+    // sums over its waves would need a slot for that one too)
+    static_assert(en_atoms(1) <= 64 && en_atoms(9) <= 64, "one wave holds a block's atoms");
+    for (int o = 32; o > 0; o >>= 1) Ui += __shfl_xor(Ui, o);
+    if (t == 0) part[blockIdx.x] = Ui;
 }
 
 // total U from the block partials (one block, fixed order)
