@@ -77,30 +77,47 @@ template <typename S, int NO> struct XRow {
         }
         __builtin_nontemporal_store(x[NO - 1], row + TAIL + lane);
     }
-    // The same through a buffer descriptor of the row: its base is wave-uniform, so
-    // that addresses cost no vector instruction, and one of no bytes (on false) reads
-    // zeros and drops stores without a branch, which would hide the number of
-    // accesses in flight from the waits that follow it.
+    // The same for FP32 and FP16 through a buffer descriptor of the row: its base is
+    // wave-uniform, so that addresses cost no vector instruction, and one of no bytes (on
+    // false) reads zeros and drops stores without a branch, which would hide the number
+    // of accesses in flight from the waits that follow it.
     static __device__ inline __amdgpu_buffer_rsrc_t row_rsrc(const S *row, bool on)
     {
         return __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, on ? NO * 64 * (int)sizeof(S) : 0, 0x00027000);
     }
-    template <int AUX, typename T> static __device__ inline void load(__amdgpu_buffer_rsrc_t r, int lane, T (&x)[NO])
+    // Raw: a lane's values as stored.  A load held in flight keeps them so: converted
+    // at once it would be waited for at once.
+    struct Raw { vec v[NP]; S tail; };
+    template <int AUX> static __device__ inline void load(__amdgpu_buffer_rsrc_t r, int lane, Raw &x)
     {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            vec v;
             if constexpr (sizeof(vec) == 16)
-                v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + p * 1024, 0, AUX));
-            else v = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(r, lane * 8 + p * 512, 0, AUX));
-#pragma unroll
-            for (int e = 0; e < V; ++e) x[p * V + e] = (T)v[e];
+                x.v[p] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + p * 1024, 0, AUX));
+            else x.v[p] = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b64(r, lane * 8 + p * 512, 0, AUX));
         }
-        if constexpr (sizeof(S) == 8)
-            x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b64(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
-        else if constexpr (sizeof(S) == 4)
-            x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
-        else x[NO - 1] = (T)__builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+        if constexpr (sizeof(S) == 4)
+            x.tail = __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b32(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+        else x.tail = __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(r, (TAIL + lane) * (int)sizeof(S), 0, AUX));
+    }
+    template <typename T> static __device__ inline void values(const Raw &r, T (&x)[NO])
+    {
+#pragma unroll
+        for (int a = 0; a < NO - 1; ++a) x[a] = (T)r.v[a / V][a % V];
+        x[NO - 1] = (T)r.tail;
+    }
+    // Wide<T>: the values converted as they arrive.
+    template <typename T> struct Wide { T x[NO]; };
+    template <int AUX, typename T> static __device__ inline void load(__amdgpu_buffer_rsrc_t r, int lane, Wide<T> &x)
+    {
+        Raw v;
+        load<AUX>(r, lane, v);
+        values(v, x.x);
+    }
+    template <typename T> static __device__ inline void values(const Wide<T> &r, T (&x)[NO])
+    {
+#pragma unroll
+        for (int a = 0; a < NO; ++a) x[a] = r.x[a];
     }
     // non-temporal
     static __device__ inline void store(__amdgpu_buffer_rsrc_t r, int lane, const S (&x)[NO])
@@ -114,9 +131,7 @@ template <typename S, int NO> struct XRow {
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, lane * 16 + p * 1024, 0, AUX_NT);
             else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, lane * 8 + p * 512, 0, AUX_NT);
         }
-        if constexpr (sizeof(S) == 8)
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
-        else if constexpr (sizeof(S) == 4)
+        if constexpr (sizeof(S) == 4)
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
         else __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, x[NO - 1]), r, (TAIL + lane) * (int)sizeof(S), 0, AUX_NT);
     }
