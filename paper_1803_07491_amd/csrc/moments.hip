@@ -952,8 +952,7 @@ template <typename T> __device__ inline void pin(T &v) { asm volatile("" : "+v"(
 
 
 
-// Rows of up to this many pairs pass their H blocks through LDS (HL): 64 lanes of
-// 16 bytes fetch them all.
+// Pairs whose d blocks one 16-byte load of 64 lanes fetches (HL).
 constexpr int HL_PAIRS = 16;
 // slots of a row whose words are held in scalar registers from a row ahead
 constexpr int SLOTS_HELD = 16;
@@ -969,12 +968,14 @@ constexpr int SLOTS_HELD = 16;
 // 204.2 ms, all results bit-identical.  Five slots in flight for d (four, six and
 // seven within 1%), two for s,p,d (three 2% slower, one 20%).
 //
-// HL: a row of up to HL_PAIRS pairs fetches its d blocks with one 16-byte load per
-// lane and passes them through LDS, which takes an eighth of the L1 accesses of
-// loading each block in the products' order (31.1 against 35.6 ms, d moments,
-// 27,648 atoms); longer rows and s,p,d (whose blocks would take six such loads and
-// 24 registers) load block by block.
-template <int NO, int WGT, int LANCZOS, typename S, bool HL, bool TR>
+// HL: d blocks of a row come with HL 16-byte loads per lane (HL_PAIRS pairs each; as
+// many as the plan's longest row needs, 1, 2 or 4) and pass through LDS, which takes an
+// eighth of the L1 accesses of loading each block in the products' order: rows of 14
+// pairs, 18 moments, 27,648 atoms 31.1 against 35.6 ms; 18 pairs, 14 moments, 6,912
+// atoms, Lanczos 7.2 against 7.6; 58 pairs, 10 moments, 3,456 atoms 7.2 against 8.0 (7.8
+// with products on the VALU).  s,p,d blocks would take six loads and 24 registers for 16
+// pairs and are loaded block by block (HL = 0).
+template <int NO, int WGT, int LANCZOS, typename S, int HL, bool TR>
 __global__ void __launch_bounds__(WGT) __attribute__((amdgpu_waves_per_eu(4, 8)))
 k_step32(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, int deg_max, int rows_cap,
        const int *__restrict__ row_ptr, const double *__restrict__ H_on, const float *__restrict__ H,
@@ -992,7 +993,7 @@ k_step32(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, in
     // converted as they arrive
     using Row = std::conditional_t<NO == 5, typename XR::Raw, typename XR::template Wide<T>>;
     __shared__ double s_red[LANCZOS ? 3 : 2][NW][64];
-    __shared__ __align__(16) float s_h[HL ? NW : 1][HL ? HL_PAIRS * NB : 4];     // a row's H blocks
+    __shared__ __align__(16) float s_h[HL ? NW : 1][HL ? HL * HL_PAIRS * NB : 4];     // a row's H blocks
     // XCD-aware numbering: block b runs on XCD b % 8; the other factor walks
     // tile-major through (tile, chunk)
     const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
@@ -1057,12 +1058,12 @@ k_step32(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, in
     };
     // a row's loads in flight: its own y'_j (X^(k-1)), r_(j-1) and r_(j-2) (zero
     // outside their supports) and the first NS neighbours with their blocks
-    u32x4_t hrow{};
+    u32x4_t hrow[HL ? HL : 1];
     Row own, r1r, r2r, x[NS];
     T h[NS][NR];
     auto gather = [&](int s, int word, int p0) {
         XR::template load<0>(XR::row_rsrc(Xp + (long)(word >> 8) * stride_row, true), lane, x[s]);
-        if constexpr (HL) return;
+        if constexpr (HL > 0) return;
         const auto hb = __builtin_amdgcn_make_buffer_rsrc((void *)(H + (long)(p0 + (word & 255)) * NB), 0,
                                                           NB * (int)sizeof(T), 0x00027000);
 #pragma unroll
@@ -1072,10 +1073,12 @@ k_step32(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, in
     };
     auto fetch = [&](int l, const Rec &m) {
         const int L = m.info & 255, nval = valid(m.info);
-        if constexpr (HL)
-            hrow = __builtin_amdgcn_raw_buffer_load_b128(
-                __builtin_amdgcn_make_buffer_rsrc((void *)(H + (long)m.p0 * NB), 0, (m.p1 - m.p0) * NB * (int)sizeof(T), 0x00027000),
-                lane * 16, 0, 0);
+        if constexpr (HL > 0) {
+            const auto hb = __builtin_amdgcn_make_buffer_rsrc((void *)(H + (long)m.p0 * NB), 0,
+                                                              (m.p1 - m.p0) * NB * (int)sizeof(T), 0x00027000);
+#pragma unroll
+            for (int i = 0; i < HL; ++i) hrow[i] = __builtin_amdgcn_raw_buffer_load_b128(hb, lane * 16 + i * 1024, 0, 0);
+        }
         XR::template load<0>(XR::row_rsrc(Xp + (long)l * stride_row, L <= k - 1), lane, own);
         if constexpr (LANCZOS) {
             XR::template load<AUX_NT>(XR::row_rsrc(Rb + (long)l * stride_row, L <= k - 2), lane, r1r);
@@ -1087,7 +1090,7 @@ k_step32(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, in
     };
     // slot s's block: in its registers, or (HL) read from the wave's LDS slice
     auto add = [&](Acc<NO> &sum, int s, int word) {
-        if constexpr (HL) {
+        if constexpr (HL > 0) {
 #pragma unroll
             for (int i = 0; i < NR; ++i) h[s][i] = s_h[w][(word & 255) * NB + hoff[i] / 4];
         }
@@ -1117,7 +1120,10 @@ k_step32(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, in
         XR::values(own, xs);
 #pragma unroll
         for (int a = 0; a < NO; ++a) acc[a] = (float)on.e[a] * xs[a];
-        if constexpr (HL) *(f32x4_t *)&s_h[w][4 * lane] = __builtin_bit_cast(f32x4_t, hrow);
+        if constexpr (HL > 0) {
+#pragma unroll
+            for (int i = 0; i < HL; ++i) *(f32x4_t *)&s_h[w][256 * i + 4 * lane] = __builtin_bit_cast(f32x4_t, hrow[i]);
+        }
         record(l + RS, atom_n, mn);
         atom_n = atom_of(l + 2 * RS);
         Acc<NO> sum;
@@ -1869,9 +1875,10 @@ int run_moments(const bop_plan &p, const int *row_ptr, const double *H_on, const
 #define BOP_STEP_TR(W, TR) \
     do { \
         if constexpr (sizeof(T) == 8) k_step<NO, W, 0, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
-        else if (NO == 5 && p.deg_max <= HL_PAIRS) \
-            k_step32<NO, W, 0, T, NO == 5, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
-        else k_step32<NO, W, 0, T, false, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
+        else if constexpr (NO != 5) k_step32<NO, W, 0, T, 0, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
+        else if (p.deg_max <= HL_PAIRS) k_step32<NO, W, 0, T, 1, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
+        else if (p.deg_max <= 2 * HL_PAIRS) k_step32<NO, W, 0, T, 2, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
+        else k_step32<NO, W, 0, T, 4, TR><<<grid, W, 0, st>>>(BOP_STEP_ARGS); \
     } while (0)
 #define BOP_STEP(W)                                                                                   \
     do {                                                                                              \
@@ -2316,9 +2323,11 @@ int run_lanczos(const bop_plan &p, const int *row_ptr, const double *H_on, const
 #define BOP_LSTEP_TR(W, TR) \
     do { \
         if constexpr (sizeof(T) == 8) k_step<NO, W, 1, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
-        else if (NO == 5 && p.deg_max <= HL_PAIRS) \
-            k_step32<NO, W, 1, S, NO == 5, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
-        else k_step32<NO, W, 1, S, false, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
+        else if constexpr (NO != 5) k_step32<NO, W, 1, S, 0, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
+        else if (sizeof(S) == 4 && p.deg_max <= HL_PAIRS) /* such FP16 rows are run_lanczos16's */ \
+            k_step32<NO, W, 1, S, sizeof(S) == 4 ? 1 : 2, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
+        else if (p.deg_max <= 2 * HL_PAIRS) k_step32<NO, W, 1, S, 2, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
+        else k_step32<NO, W, 1, S, 4, TR><<<grid, W, 0, st>>>(BOP_LSTEP_ARGS); \
     } while (0)
 #define BOP_LSTEP(W)                                                                                  \
     do {                                                                                              \
