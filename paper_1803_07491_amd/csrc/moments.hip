@@ -954,8 +954,6 @@ template <typename T> __device__ inline void pin(T &v) { asm volatile("" : "+v"(
 
 // Pairs whose d blocks one 16-byte load of 64 lanes fetches (HL).
 constexpr int HL_PAIRS = 16;
-// slots of a row whose words are held in scalar registers from a row ahead
-constexpr int SLOTS_HELD = 16;
 
 // The same step (k_step: rows, sums and their order are its own) for FP32, and for
 // vectors stored in FP16 (S).  What bounds it is the traffic between L2 and memory
@@ -1034,7 +1032,9 @@ k_step32(Batch bt, int k, int K, int last, int keep, int nch, int chunk_rows, in
         linv = (T)l[256];
     }
     // What a row's pass needs to know of it, by scalar loads a row ahead of their
-    // use (the atom, whose pair range takes a second load, two rows ahead).
+    // use (the atom, whose pair range takes a second load, two rows ahead).  The words
+    // past a row's own are not used; where rows have fewer than SLOTS_HELD slots the last
+    // ones' reads go past the slot list, which make_layout has room for.
     struct Rec { int atom, info, mask, p0, p1, word[SLOTS_HELD]; };
     auto atom_of = [&](int l) { return cst(sup)[min(l, nrow - 1)]; };
     auto record = [&](int l, int atom, Rec &m) {

@@ -14,6 +14,7 @@ constexpr int MAXK = MAX_NMAX / 2;
 constexpr int HDR = 256;            // header ints: [0] queue, [1] error, [2] max rows, [3] max degree,
                                     // [8 + k] max rows of U^k (plan)
 constexpr int LC_N = 8;             // Lanczos column coefficients per lane and tile
+constexpr int SLOTS_HELD = 16;      // slots of a row whose words k_step32 holds in scalar registers from a row ahead
 
 // Row assignment of the step kernels: a tile with nrow rows at this step uses
 // nct = tile_chunks(..) of the launch's chunks, and chunk c < nct takes the
@@ -201,6 +202,10 @@ __host__ __device__ inline Layout make_layout(const bop_plan &p, int n_prep_wg)
     L.sizes = take(4ull * p.n_tiles * (MAXK + 2));
     L.tile_stride = (4ull * p.rows_cap * (3 + p.deg_max) + 255) / 256 * 256;   // sup, rinfo, lnb, row masks
     L.tiles = take(L.tile_stride * p.n_tiles);
+    // Keep something of SLOTS_HELD ints or more behind the tile records: k_step32 reads that
+    // many words of every row's slot list, so past the last record where rows are few and
+    // short (8 rows of 5 slots end 12 bytes short).  The X buffers take a row of 640 bytes
+    // at least.
     L.x_stride = (x_row_bytes(p.dtype, p.n_orb) * p.rows_cap + 255) / 256 * 256;
     size_t xb = L.x_stride * (p.batch_tiles >= 2 ? 2 * (size_t)p.batch_tiles : 4);
     size_t maps = (size_t)n_prep_wg * ((4ull * p.n_atoms + 255) / 256 * 256);
