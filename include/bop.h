@@ -367,9 +367,13 @@ int bop_recursion(int n_rows, int n_max, const double *mu, int bw_mode,
  *             2 sum N_ia(E) = n_elec over [min(a_inf - 2 b_inf), max(a_inf +
  *             2 b_inf)]: twelve halvings, then interpolation between counts
  *             closer and closer to the root, whose bracket E_F lies in to the
- *             counts' rounding.  Where the count is all but flat the halving
- *             goes on while the midpoint differs from both ends (at most 64
- *             times) and E_F = midpoint of the final bracket.
+ *             counts' rounding.  Where the count is all but flat, not smooth over
+ *             the last 4096th of the band, or seen to pass n_elec there more than
+ *             once, the halving goes on while the midpoint differs from both ends
+ *             (at most 64 times) and E_F = midpoint of the final bracket: the root
+ *             of a count that is not monotone is bisection's.  (A turn of a smooth
+ *             count between the 15 energies that a pass counts at is not seen; E_F
+ *             is then a root of the same 4096th of the band.)
  *  ef_mode 1: E_F [device] in: energies at the given level.
  *  ws: bop_energy_workspace_size(n_atoms, n_orb, n_exp) bytes.
  *  n_exp <= 1024 (default used by the paper's example: 200); n_orb <= 9

@@ -512,8 +512,7 @@ k_bracket_pick(int n_rows, unsigned n_blocks, const double *__restrict__ part, F
 //  * bisecting passes (the first FT_TREE, and all after the closing ones): the nodes
 //    are the midpoints that the next four halvings can visit, a binary tree in heap
 //    order formed exactly as sequential bisection forms it, mid = (lo + hi)/2, and
-//    the four decisions are replayed.  They, and so the root found when the count
-//    is not monotone, are those of plain bisection;
+//    the four decisions are replayed.  They are those of plain bisection;
 //  * after FT_TREE passes the count is smooth on the bracket, a 4096th of the band (its
 //    200 or so terms turn by a seventh of a radian over the pass's node spacing):
 //    the polynomial through the eight nodes nearest to the sign change gives its root
@@ -526,7 +525,12 @@ k_bracket_pick(int n_rows, unsigned n_blocks, const double *__restrict__ part, F
 //  * a count that is all but flat on the bracket (a gap, next to no or all electrons),
 //    where the level depends on the counts' rounding, is bisected throughout, to
 //    the last bit or FT_MAX_HALVINGS, and so is what the closing passes left open
-//    (a band edge in the bracket).
+//    (a band edge in the bracket);
+//  * so is a count that the polynomial does not follow (rows whose band is a small
+//    part of the others', diverging expansions), and one that a closing pass finds
+//    above n_elec and below it again.  Where the count has several roots the level
+//    is therefore plain bisection's, unless the count is smooth at its nodes and all of
+//    a closing pass's nodes miss its turn.
 // Four passes then do for what bisection alone takes 15 for.  Against it the level is
 // within 1e-15 eV over 54 to 27,648 atoms and 1 to 1024 terms; whole tails, 200 terms: 128
 // atoms 168 -> 130 us, 2000 atoms 326 -> 177, 8192 atoms 590 -> 308, 128,000 atoms 6.16 ->
@@ -539,6 +543,9 @@ constexpr double FT_TIGHT = 1.0 / (1 << 24);
 // rounding then moves the level by less than 1e-12 of the band.  (A count that is
 // reached at the bracket's very end may be reached there without slope.)
 constexpr double FT_SLOPE = 1e-7;
+// Rounding of a count, relative to the rows or, where expansions diverge, to the counts
+// at the bracket's ends: what a node past the root may lie below n_elec by.
+constexpr double FT_ROUND = 1.0 / (1ull << 44);
 constexpr int FP_ROWS = 32;                    // rows per row block (one per lane of half a wave)
 constexpr int FP_GROUPS = DT / FP_ROWS;        // thread groups of a block, each with its own nodes
 constexpr int FP_RUN = 26;                     // coefficients a thread stages
@@ -570,7 +577,9 @@ __device__ inline double node_energy(const FermiState &st, int pass, int p)
 }
 
 // Root in [i, i + 1] of the polynomial through eight of the 17 equally spaced values
-// v (Newton's form on forward differences, a few safeguarded Newton steps).
+// v (Newton's form on forward differences, a few safeguarded Newton steps); -1 where the
+// differences do not fall off: with a seventh difference above the step from v[i] to
+// v[i + 1] the closing passes take as long as bisection, or longer.
 __device__ inline double root_between(const double *v, int i, double n_elec)
 {
     const int j0 = min(max(i - 3, 0), FT_NODES + 1 - 7);
@@ -582,6 +591,7 @@ __device__ inline double root_between(const double *v, int i, double n_elec)
     for (int k = 1; k < 8; ++k)
 #pragma unroll
         for (int q = 7; q >= k; --q) d[q] -= d[q - 1];
+    if (!(fabs(d[7]) <= fh - fl)) return -1.0;
     const double a = i - j0;
     double u = a + fl / (fl - fh);
     for (int it = 0; it < 5; ++it) {
@@ -629,9 +639,20 @@ __device__ inline FermiState fermi_advance(const FermiState &st, int pass, int n
             v[q] = 2.0 * tot[(1 << (FT_LEVELS - 1 - z)) + (q >> (z + 1)) - 1];
         }
         frac = root_between(v, node - (1 << FT_LEVELS), n_elec);
+        if (frac < 0.0) {
+            s.plain = 1.0;
+            return s;
+        }
     } else {
         int j = 0;
         while (j < FT_NODES && 2.0 * tot[j] < n_elec) ++j;
+        const double slack = FT_ROUND * fmax((double)n_rows, fmax(fabs(st.nlo), fabs(st.nhi)));
+        bool once = true;
+        for (int q = j + 1; q < FT_NODES; ++q) once = once && 2.0 * tot[q] >= n_elec - slack;
+        if (!once) {
+            s.plain = 1.0;
+            return s;
+        }
         if (j < FT_NODES) { s.hi = node_energy(st, pass, j); s.nhi = 2.0 * tot[j]; }
         if (j > 0) { s.lo = node_energy(st, pass, j - 1); s.nlo = 2.0 * tot[j - 1]; }
         frac = (n_elec - s.nlo) / (s.nhi - s.nlo);
