@@ -528,7 +528,9 @@ k_bracket_pick(int n_rows, unsigned n_blocks, const double *__restrict__ part, F
 //    (a band edge in the bracket);
 //  * so is a count that the polynomial does not follow (rows whose band is a small
 //    part of the others', diverging expansions), and one that a closing pass finds
-//    above n_elec and below it again.  Where the count has several roots the level
+//    above n_elec and below it again.  A closing pass that narrows the bracket by less
+//    than a bisecting one is the last, so that the FT_PASSES passes of plain bisection do
+//    for every search (one such pass in it, they reach a 2^60th of the band).  Where the count has several roots the level
 //    is therefore plain bisection's, unless the count is smooth at its nodes and all of
 //    a closing pass's nodes miss its turn.
 // Four passes then do for what bisection alone takes 15 for.  Against it the level is
@@ -657,6 +659,7 @@ __device__ inline FermiState fermi_advance(const FermiState &st, int pass, int n
         if (j > 0) { s.lo = node_energy(st, pass, j - 1); s.nlo = 2.0 * tot[j - 1]; }
         frac = (n_elec - s.nlo) / (s.nhi - s.nlo);
         if (s.hi - s.lo <= FT_TIGHT * (st.hi - st.lo)) s.done = 1.0;
+        else if ((1 << FT_LEVELS) * (s.hi - s.lo) > st.hi - st.lo) s.plain = 1.0;
     }
     if (!(frac >= 0.0 && frac <= 1.0)) frac = 0.5;
     s.x = s.lo + frac * (s.hi - s.lo);
@@ -962,11 +965,11 @@ k_fermi_finish(int n_rows, int pass, double n_elec, const double *__restrict__ p
 // Rows up to which k_fermi_pass makes the search's passes, k_fermi_tree beyond: 26 us
 // against 42 at 40,960 rows, 101 against 76 at 138,240.
 constexpr long FT_SPREAD = 65536;
-// Passes after the closing ones, which find nothing to do where those closed the bracket:
-// every halving that can be left.  (One block doing what is left instead saves their 40
-// us, but takes 1.1 ms for 1000 rows with a gap, where they take 0.2 and bisecting all the
-// way took 0.67.)
-constexpr int FT_REST = (FT_MAX_HALVINGS - FT_TREE * FT_LEVELS) / FT_LEVELS;
+// Passes of a search: every halving of plain bisection.  Passes that find the bracket
+// closed cost a small structure 35 us of its tail.  (One block doing what is left instead
+// saves those, but takes 1.1 ms for 1000 rows with a gap, where they take 0.2 and
+// bisecting all the way took 0.67.)
+constexpr int FT_PASSES = FT_MAX_HALVINGS / FT_LEVELS;
 
 // The search.  Up to FT_FUSED rows, two trees of sums per node, each block replays the
 // previous decisions and `states` holds every pass's state.  `tree` holds the 32-row
@@ -976,18 +979,17 @@ static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs,
                          const double *b_inf, unsigned n_bracket, double *part, double *tree, FermiState *st,
                          FermiState *states, double *E_F, hipStream_t stream)
 {
-    const int passes = FT_TREE + FT_CLOSE + FT_REST;
     const unsigned n_rb = (unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS), n_tb = (unsigned)((2L * n_rows + DT - 1) / DT);
     if (tree && n_rows <= FT_FUSED) {
         double *buf[2] = {tree, tree + ft_pitch(n_rb) * (FT_NODES + 1)};
-        for (int it = 0; it < passes; ++it)
+        for (int it = 0; it < FT_PASSES; ++it)
             k_fermi_pass<true><<<n_rb, DT, 0, stream>>>(n_rows, n_exp, it, n_bracket, n_elec, gs, a_inf, b_inf,
                                                         it ? buf[(it - 1) & 1] : part, buf[it & 1], states);
-        k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, passes, n_elec, buf[(passes - 1) & 1], states, E_F);
+        k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, FT_PASSES, n_elec, buf[(FT_PASSES - 1) & 1], states, E_F);
         return;
     }
     k_bracket_pick<<<1, DT, 0, stream>>>(n_rows, n_bracket, part, st);
-    for (int it = 0; it < passes; ++it) {
+    for (int it = 0; it < FT_PASSES; ++it) {
         if (tree) {
             k_fermi_pass<false><<<n_rb, DT, 0, stream>>>(n_rows, n_exp, it, 0, n_elec, gs, a_inf, b_inf, nullptr, tree,
                                                          st);
@@ -997,7 +999,7 @@ static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs,
             k_fermi_pick<1><<<1, FT_PICK * DT, 0, stream>>>(n_tb, it, n_rows, n_elec, part, st);
         }
     }
-    k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, passes, n_elec, nullptr, st, E_F);
+    k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, FT_PASSES, n_elec, nullptr, st, E_F);
 }
 
 // per-atom N, U, n(E_F) and block partials of U.  A row's sums over its 200 or so
@@ -1158,7 +1160,7 @@ EnergyWs carve(void *base, long n_rows, int n_exp)
     if (n_rows <= FT_SPREAD) {
         const size_t rb = ft_pitch((unsigned)((n_rows + FP_ROWS - 1) / FP_ROWS));
         w.tree = (double *)take(sizeof(double) * 2 * rb * (FT_NODES + 1));
-        w.states = (FermiState *)take(sizeof(FermiState) * (FT_TREE + FT_CLOSE + FT_REST));
+        w.states = (FermiState *)take(sizeof(FermiState) * FT_PASSES);
     }
     w.bytes_tree = (size_t)(p - (char *)base);
     return w;
