@@ -1002,33 +1002,47 @@ static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs,
     k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, FT_PASSES, n_elec, nullptr, st, E_F);
 }
 
-// per-atom N, U, n(E_F) and block partials of U.  A row's sums over its 200 or so
-// terms are split over EN_SEGS threads, each starting its run of terms from its own
-// power of the rotation, with the run's coefficients in flight together: a single thread
-// per row waits for one memory access after another and for one rotation after another.
-// An atom's orbitals are then added in orbital order, as a per-atom loop would
-// add them.  200 terms: 128 atoms 69 -> 8 us, 8192 atoms 75 -> 19, 128,000 atoms 295 ->
-// 225 (its coefficients at 4.6 TB/s); eight runs per row instead of four: 7, 28 and 459.
-constexpr int EN_SEGS = 4, EN_RUN = 13;          // runs per row, coefficients loaded at once
-// atoms per block
-__host__ __device__ constexpr int en_atoms(int no) { return no <= 2 ? 16 : 8; }
-constexpr int EN_MAXT = 8 * 9 * EN_SEGS;
-constexpr int EN_TAB = 3 + EN_SEGS + EN_RUN;     // table entries past n_exp that the last run can reach
+// per-atom N, U, n(E_F) and block partials of U.  Where rows are few, a row's sums over
+// its 200 or so terms are split over SEGS = 4 threads, each starting its run of terms from
+// its own power of the rotation: a single thread per row waits for one memory access after
+// another and for one rotation after another.  Where the rows fill the chip the runs'
+// starts (square roots, arccosines, powers) are work on top, and a thread takes a row.
+// Either way a run's coefficients are loaded EN_RUN at a time, all in flight.  An atom's
+// orbitals are then added in orbital order, as a per-atom loop would add them.
+// 200 terms, four runs: 128 atoms 69 -> 8 us, 8192 atoms 75 -> 19 (one run: 27; eight: 28).
+constexpr int EN_RUN = 13;                       // coefficients loaded at once
+// Atoms per block: one run, 9 orbitals, 30,000 atoms, 75 terms 35 us with 64 (nine whole
+// waves), 46 with 32; 5 orbitals, 40,000 atoms 37 with 64, 25 with 32.
+__host__ __device__ constexpr int en_atoms(int no, int segs)
+{
+    return segs == 4 ? (no <= 2 ? 16 : 8) : (no > 4 && no < 9 ? 32 : 64);
+}
+constexpr int EN_FOUR = 8 * 9 * 4, EN_ONE = 32 * 8, EN_ONE9 = 64 * 9;     // most threads of a block
+// One run from EN_FULL rows on, for long expansions from EN_MEMORY on.  Expansion and sums
+// together, one against four runs: 9 orbitals, 270,000 rows, 25 terms 60 and 101 us, 75
+// terms 130 and 176, 200 terms 349 and 382; 5 orbitals, 100,000 rows, 25 terms 38 and 44,
+// 200 terms 155 and 154; 200,000 rows, 200 terms 301 and 289 (while the coefficients come
+// from the cache, four runs' loads are worth their starts); 40,960 rows, 25 terms 26 and 29;
+// 10,000 rows, 150 terms 40 and 33.
+constexpr long EN_FULL = 32768, EN_MEMORY = 250000;
+constexpr int EN_SHORT = 160;
+constexpr int EN_TAB = 3 + 4 + EN_RUN;           // table entries past n_exp that the last run can reach
 
-__global__ void __launch_bounds__(EN_MAXT)
+template <int SEGS, int MAXT>
+__global__ void __launch_bounds__(MAXT)
 k_energy(int n_atoms, int no, int n_exp, double wt, const double *__restrict__ gs, const double *__restrict__ a_inf,
          const double *__restrict__ b_inf, const double *__restrict__ H_on, const double *__restrict__ E_F,
          double *__restrict__ N_atom, double *__restrict__ U_atom, double *__restrict__ dos_atom,
          int *__restrict__ flags, double *__restrict__ part)
 {
-    __shared__ double s_inv[1024 + EN_TAB], s_s[3][EN_MAXT];
-    const int EA = en_atoms(no), RB = EA * no;
+    __shared__ double s_inv[1024 + EN_TAB], s_s[3][MAXT];
+    const int EA = en_atoms(no, SEGS), RB = EA * no;
     const int row = threadIdx.x % RB, seg = threadIdx.x / RB;
     const long n_rows = (long)n_atoms * no;
     const long r = (long)blockIdx.x * RB + row;
     const bool live = r < n_rows;
     const long rr = live ? r : n_rows - 1;
-    const int T = (n_exp + EN_SEGS) / EN_SEGS;   // of the n_exp + 1 terms, per run
+    const int T = (n_exp + SEGS) / SEGS;         // of the n_exp + 1 terms, per run
     const int m0 = seg * T, m1 = min(m0 + T, n_exp + 1);
     double g[EN_RUN];
     auto fetch = [&](int m) {
@@ -1092,7 +1106,7 @@ k_energy(int n_atoms, int no, int n_exp, double wt, const double *__restrict__ g
     s_s[2][threadIdx.x] = D;
     __syncthreads();
     if (seg == 0) {
-        for (int q = 1; q < EN_SEGS; ++q) {
+        for (int q = 1; q < SEGS; ++q) {
             N += s_s[0][q * RB + row];
             U += s_s[1][q * RB + row];
             D += s_s[2][q * RB + row];
@@ -1124,7 +1138,7 @@ k_energy(int n_atoms, int no, int n_exp, double wt, const double *__restrict__ g
     }
     // the block's atoms are in its first wave (a block may end in part of a wave, so
     // sums over its waves would need a slot for that one too)
-    static_assert(en_atoms(1) <= 64 && en_atoms(9) <= 64, "one wave holds a block's atoms");
+    static_assert(en_atoms(1, SEGS) <= 64 && en_atoms(9, SEGS) <= 64, "one wave holds a block's atoms");
     for (int o = 32; o > 0; o >>= 1) Ui += __shfl_xor(Ui, o);
     if (t == 0) part[blockIdx.x] = Ui;
 }
@@ -1239,9 +1253,11 @@ static int energy_impl(int n_atoms, int no, int n_max, int n_exp, const double *
                      stream);
         BOP_LAUNCHED();
     }
-    const unsigned ablk = (unsigned)((n_atoms + en_atoms(no) - 1) / en_atoms(no));
-    k_energy<<<ablk, en_atoms(no) * no * EN_SEGS, 0, stream>>>(n_atoms, no, n_exp, wt, w.gs, a_inf, b_inf, H_on, E_F, N_atom, U_atom,
-                                      dos_atom, flags, w.part);
+    const int segs = R >= EN_FULL && (n_exp < EN_SHORT || R >= EN_MEMORY) ? 1 : 4, ea = en_atoms(no, segs);
+    const unsigned ablk = (unsigned)((n_atoms + ea - 1) / ea);
+    auto *energy = segs == 4 ? k_energy<4, EN_FOUR> : (no < 9 ? k_energy<1, EN_ONE> : k_energy<1, EN_ONE9>);
+    energy<<<ablk, ea * no * segs, 0, stream>>>(n_atoms, no, n_exp, wt, w.gs, a_inf, b_inf, H_on, E_F, N_atom, U_atom,
+                                                dos_atom, flags, w.part);
     k_energy_total<<<1, DT, 0, stream>>>(ablk, w.part, U_total);
     BOP_LAUNCHED();
     return BOP_OK;
