@@ -835,9 +835,10 @@ __global__ void __launch_bounds__(DT)
 k_fermi_tree(int n_rows, int n_exp, int pass, const double *__restrict__ gs, const double *__restrict__ a_inf,
              const double *__restrict__ b_inf, double *__restrict__ part, const FermiState *st)
 {
-    __shared__ double s_inv[1040], s_red[FT_NODES * (DT / 64)];
+    __shared__ double s_inv[1040], s_red[FT_NODES * (DT / 64)], s_mid[FT_NODES];
     if (st->done != 0.0) return;
-    const FermiState now = *st;
+    // by every lane for its own nodes: 44 against 40 us a pass, 320,000 rows, 10 terms
+    if (threadIdx.x < FT_NODES) s_mid[threadIdx.x] = node_energy(*st, pass, threadIdx.x);
     for (int k = threadIdx.x; k <= n_exp + 2; k += blockDim.x) s_inv[k] = k ? 1.0 / k : 0.0;
     __syncthreads();
     const long gt = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -853,7 +854,7 @@ k_fermi_tree(int n_rows, int n_exp, int pass, const double *__restrict__ gs, con
 #pragma unroll
             for (int j = 0; j < FT_HALF; ++j) {
                 const int p = h * FT_HALF + j < FT_NODES ? h * FT_HALF + j : FT_NODES - 1;
-                double eps = (node_energy(now, pass, p) - ai) / (2.0 * bi);
+                double eps = (s_mid[p] - ai) / (2.0 * bi);
                 twoc[j] = 2.0 * (eps < -1.0 ? -1.0 : (eps > 1.0 ? 1.0 : eps));
                 b1[j] = 0.0;
                 b2[j] = 0.0;
@@ -900,16 +901,18 @@ k_fermi_tree(int n_rows, int n_exp, int pass, const double *__restrict__ gs, con
 // block): every node's sums (Q partials in turn) in a fixed order, thread t of DT
 // taking sums t, t + DT, ..., then the fixed tree.  The nodes are dealt to FT_PICK such
 // sets of threads, and a thread's loads are in flight together: one block waits for
-// memory, not for its bandwidth.
+// memory, not for its bandwidth.  AHEAD such loads: as many as there are sums for (eight
+// where one will do took 6.3 us against 4.4, 50,000 rows).
 constexpr int FT_PICK = 4;
 
-template <int Q>
+template <int Q, int AHEAD>
 __global__ void __launch_bounds__(FT_PICK * DT)
 k_fermi_pick(unsigned n_rb, int pass, int n_rows, double n_elec, const double *__restrict__ part, FermiState *st)
 {
-    constexpr int NPT = (FT_NODES + FT_PICK - 1) / FT_PICK, NW = DT / 64, AHEAD = 8 / Q;
+    constexpr int NPT = (FT_NODES + FT_PICK - 1) / FT_PICK, NW = DT / 64;
     __shared__ double s_red[FT_PICK][NPT * NW], s_tot[FT_PICK * NPT], s_v[FT_NODES + 2];
-    if (st->done != 0.0) return;
+    const FermiState was = *st;                              // comes while the partials do
+    if (was.done != 0.0) return;
     const unsigned t = threadIdx.x % DT, set = threadIdx.x / DT, n = (n_rb + Q - 1) / Q;
     const size_t pitch = Q == 1 ? n_rb : ft_pitch(n_rb);
     double acc[NPT];
@@ -948,7 +951,7 @@ k_fermi_pick(unsigned n_rb, int pass, int n_rows, double n_elec, const double *_
         s_tot[set * NPT + t] = v;
     }
     __syncthreads();
-    if (threadIdx.x == 0) *st = fermi_advance(*st, pass, n_rows, n_elec, s_tot, s_v);
+    if (threadIdx.x == 0) *st = fermi_advance(was, pass, n_rows, n_elec, s_tot, s_v);
 }
 
 // The level, by one block: where the blocks replay the decisions, after the last pass's
@@ -962,9 +965,21 @@ k_fermi_finish(int n_rows, int pass, double n_elec, const double *__restrict__ p
     if (threadIdx.x == 0) E_F[0] = 0.5 * (now.lo + now.hi);
 }
 
-// Rows up to which k_fermi_pass makes the search's passes, k_fermi_tree beyond: 26 us
-// against 42 at 40,960 rows, 101 against 76 at 138,240.
-constexpr long FT_SPREAD = 65536;
+// Rows up to which k_fermi_pass makes the search's passes, k_fermi_tree beyond; fewer where
+// the expansions are short: the pass stages 202 terms or none, three blocks to a CU, and
+// a block's time passes for every 768 blocks or part of them (rounds).  Whole
+// tails bisecting all the way, pass form and tree: 24,000 rows, 10 terms 233 and 226 us, 25
+// terms 242 and 248; 41,000 rows, 50 terms 391 and 359, 75 terms 412 and 431; 57,000 rows, 75
+// terms 471 and 447, 100 terms 516 and 518; 65,500 rows, 150 terms 654 and 628, 200 terms 745
+// and 768.
+constexpr long FT_SPREAD = 65536, FT_RESIDENT = 3 * 256 * FP_ROWS;
+
+static bool pass_form(long n_rows, int n_exp)
+{
+    if (n_rows <= FT_FUSED) return true;
+    const long rounds = (n_rows + FT_RESIDENT - 1) / FT_RESIDENT;
+    return n_rows <= FT_SPREAD && n_exp >= (rounds <= 1 ? 20 : (rounds == 2 ? 64 : 128));
+}
 // Passes of a search: every halving of plain bisection.  Passes that find the bracket
 // closed cost a small structure 35 us of its tail.  (One block doing what is left instead
 // saves those, but takes 1.1 ms for 1000 rows with a gap, where they take 0.2 and
@@ -973,7 +988,7 @@ constexpr int FT_PASSES = FT_MAX_HALVINGS / FT_LEVELS;
 
 // The search.  Up to FT_FUSED rows, two trees of sums per node, each block replays the
 // previous decisions and `states` holds every pass's state.  `tree` holds the 32-row
-// partials of two passes in turn; NULL for more than FT_SPREAD rows and where the
+// partials of two passes in turn; NULL where not pass_form and where the
 // caller's workspace has no room for it.
 static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs, const double *a_inf,
                          const double *b_inf, unsigned n_bracket, double *part, double *tree, FermiState *st,
@@ -993,10 +1008,12 @@ static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs,
         if (tree) {
             k_fermi_pass<false><<<n_rb, DT, 0, stream>>>(n_rows, n_exp, it, 0, n_elec, gs, a_inf, b_inf, nullptr, tree,
                                                          st);
-            k_fermi_pick<4><<<1, FT_PICK * DT, 0, stream>>>(n_rb, it, n_rows, n_elec, tree, st);
+            auto *pick = n_rb <= 4 * DT ? k_fermi_pick<4, 1> : k_fermi_pick<4, 2>;
+            pick<<<1, FT_PICK * DT, 0, stream>>>(n_rb, it, n_rows, n_elec, tree, st);
         } else {
             k_fermi_tree<<<n_tb, DT, 0, stream>>>(n_rows, n_exp, it, gs, a_inf, b_inf, part, st);
-            k_fermi_pick<1><<<1, FT_PICK * DT, 0, stream>>>(n_tb, it, n_rows, n_elec, part, st);
+            auto *pick = n_tb <= DT ? k_fermi_pick<1, 1> : (n_tb <= 2 * DT ? k_fermi_pick<1, 2> : k_fermi_pick<1, 8>);
+            pick<<<1, FT_PICK * DT, 0, stream>>>(n_tb, it, n_rows, n_elec, part, st);
         }
     }
     k_fermi_finish<<<1, DT, 0, stream>>>(n_rows, FT_PASSES, n_elec, nullptr, st, E_F);
@@ -1248,7 +1265,7 @@ static int energy_impl(int n_atoms, int no, int n_max, int n_exp, const double *
         // a workspace without the tree's partials (of the size earlier versions asked
         // for, or the fixed array at its limit) takes the route of many rows
         const double ne = n_elec / wt;
-        const bool tree = R <= FT_SPREAD && ws_bytes >= w.bytes_tree;
+        const bool tree = pass_form(R, n_exp) && ws_bytes >= w.bytes_tree;
         fermi_search((int)R, n_exp, ne, w.gs, a_inf, b_inf, nblk, w.part, tree ? w.tree : nullptr, w.st, w.states, E_F,
                      stream);
         BOP_LAUNCHED();
