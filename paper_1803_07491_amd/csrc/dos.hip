@@ -1024,8 +1024,9 @@ static void fermi_search(int n_rows, int n_exp, double n_elec, const double *gs,
 // its own power of the rotation: a single thread per row waits for one memory access after
 // another and for one rotation after another.  Where the rows fill the chip the runs'
 // starts (square roots, arccosines, powers) are work on top, and a thread takes a row.
-// Either way a run's coefficients are loaded EN_RUN at a time, all in flight.  An atom's
-// orbitals are then added in orbital order, as a per-atom loop would add them.
+// Either way a run's coefficients are loaded EN_RUN at a time, all in flight, and summed
+// among themselves first (N of 201 terms: 1.6e-16 from its value in the mean with one run or
+// four, 4e-16 as one chain).  An atom's orbitals are then added in orbital order, as a per-atom loop would add them.
 // 200 terms, four runs: 128 atoms 69 -> 8 us, 8192 atoms 75 -> 19 (one run: 27; eight: 28).
 constexpr int EN_RUN = 13;                       // coefficients loaded at once
 // Atoms per block: one run, 9 orbitals, 30,000 atoms, 75 terms 35 us with 64 (nine whole
@@ -1102,18 +1103,22 @@ k_energy(int n_atoms, int no, int n_exp, double wt, const double *__restrict__ g
     double chi1 = m0 == 0 ? x1 : w2 * s_inv[m0 + 2] - S * s_inv[m0];
     double N = 0.0, U = 0.0, D = 0.0;
     for (int mb = m0;;) {
+        double n = 0.0, u = 0.0, d = 0.0;
 #pragma unroll
         for (int t = 0; t < EN_RUN; ++t) {
             const int m = mb + t;
             const double chi2 = w3 * s_inv[m + 3] - w1 * s_inv[m + 1];
-            N = fma(g[t], chi1, N);
-            U = fma(g[t], chi2 + chi0, U);
-            D = fma(g[t], w1, D);
+            n = fma(g[t], chi1, n);
+            u = fma(g[t], chi2 + chi0, u);
+            d = fma(g[t], w1, d);
             chi0 = chi1;
             chi1 = chi2;
             const double nc = c3 * c - w3 * s, ns = w3 * c + c3 * s;
             w1 = w2; w2 = w3; w3 = ns; c3 = nc;
         }
+        N += n;
+        U += u;
+        D += d;
         mb += EN_RUN;
         if (mb - m0 >= T) break;                 // the same for every thread
         fetch(mb);
