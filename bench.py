@@ -176,6 +176,13 @@ def read_traffic(dtype, method, source="moments.hip"):
     return d.get("bytes_per_launch")
 
 
+def hx_kernel(dtype, method):
+    """The step kernel of an H.X pass over the d band (rows of up to 16 pairs)."""
+    if method == "lanczos" and dtype in ("bf16", "f16"):
+        return "k_lstep16"
+    return {"f64": "k_step", "bf16": "k_step_bf16"}.get(dtype, "k_step32")
+
+
 def per_atom_errors(out, ref):
     """Largest relative per-atom differences of N_i and U_i."""
     eN = ((out["N_atom"] - ref["N_atom"]).abs() / ref["N_atom"].abs()).max().item()
@@ -284,7 +291,7 @@ def hx_roofline(P, wl, dtype, method, torch):
     ach = flops / (kms * 1e-3) / 1e12
     return {"bound": "alu", "achieved": ach, "peak": PEAK_TFLOPS[dtype], "unit": "TFLOP/s",
             "frac": ach / PEAK_TFLOPS[dtype], "traffic": None,
-            "kernel": f"k_step ({method}, {dtype}): the H.X launches of one energy pass of the cell",
+            "kernel": f"{hx_kernel(dtype, method)} ({method}, {dtype}): the H.X launches of one energy pass of the cell",
             "kernel_ms": kms, "algorithmic_flops_per_launch": flops, "flops_per_atom": float(fpa.mean())}
 
 
@@ -389,8 +396,8 @@ def main():
         "roofline": {"bound": "mfma" if args.dtype in ("bf16", "f16") else "alu", "achieved": achieved, "peak": peak,
                      "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": traffic,
-                     "kernel": ("k_lstep16" if args.dtype in ("bf16", "f16") and args.method == "lanczos" else "k_step")
-                               + " (all H.X launches of one pass)", "kernel_ms": t_mom_ms,
+                     "kernel": hx_kernel(args.dtype, args.method) + " (all H.X launches of one pass)",
+                     "kernel_ms": t_mom_ms,
                      "algorithmic_flops_per_launch": flops,
                      "flops_per_atom": float(fpa.mean()), "flops_per_atom_spread": float(np.ptp(fpa))},
     }
@@ -780,7 +787,7 @@ def bench_radius(args, torch, P, W):
     ach = flops / (best[1]["hx_ms"] * 1e-3) / 1e12
     res["roofline"] = {"bound": "alu", "achieved": ach, "peak": PEAK_TFLOPS["f32"], "unit": "TFLOP/s",
                        "frac": ach / PEAK_TFLOPS["f32"], "traffic": None,
-                       "kernel": f"k_step with a path radius of {best[0]} A (all H.X launches of one pass)",
+                       "kernel": f"k_step32 with a path radius of {best[0]} A (all H.X launches of one pass)",
                        "kernel_ms": best[1]["hx_ms"], "algorithmic_flops_per_launch": flops,
                        "flops_per_atom": float(fpa.mean())}
     if not args.no_cpu:

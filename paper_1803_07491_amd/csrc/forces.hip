@@ -175,8 +175,10 @@ __device__ inline int fb_of(int n_max) { return n_max / 2; }
 // For n_max <= NM, every loop over moments and levels unrolled, so that no array is
 // indexed at run time: arrays in scratch memory took most of the time.  Unrolled, with
 // the tables built by a lane per column, same bits: 250 atoms at 10 moments 272 -> 143 us,
-// at 18 490 -> 233; 11,664 atoms at 18 6.90 -> 2.75 ms, at 10 1.90 -> 1.01.  Two waves
-// per SIMD, with spills at 18 (one: 211 us and 3.06 ms); one at 20, where two spill
+// at 18 490 -> 233; 11,664 atoms at 18 6.90 -> 2.75 ms, at 10 1.90 -> 1.01.  Orders between
+// the forms take the next one's registers: 3,456 atoms at 11 0.72 -> 0.46 ms, at 12 1.00 ->
+// 0.61, at 14 1.19 -> 0.62, at 16 1.77 -> 0.79, at 19 3.85 -> 1.23, at 7 0.38 -> 0.20.  Two
+// waves per SIMD, with spills at 18 (one: 211 us and 3.06 ms); one at 20, where two spill
 // most of the recursion (240 against 385 us, 128 atoms).
 template <int NM>
 __global__ void __launch_bounds__(WT) __attribute__((amdgpu_waves_per_eu(NM <= 18 ? 2 : 1, 8)))
@@ -704,8 +706,8 @@ k_fstep(FBatch bt, int lev, int n, int K, int nch, int chunk_rows, int deg_max, 
             }
             __builtin_amdgcn_wave_barrier();
         }
-        // column sums of the contracted slots held in the wave's LDS block (nc of
-        // them, the latest slot s1, the one before it sp) into the row's pair sums
+        // column sums of the contracted slots held in the wave's LDS block (nc of them:
+        // slot s_a in its rows 0 .. 2, s_b in rows 3 .. 5) into the row's pair sums
         double *sp_row = &s_pair[BWD ? wv : 0][0];
         int nc = 0, s_a = 0, s_b = 0;
         auto column_sums = [&]() {

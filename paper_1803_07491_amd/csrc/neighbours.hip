@@ -212,7 +212,7 @@ __device__ inline void scan_atom(const Geom &g, int n, int i, int l, const doubl
 constexpr int NL = 32;              // lanes per atom
 constexpr int NT = 256;             // threads per block
 constexpr int NA = NT / NL;         // atoms per block
-constexpr int NROW = 256;           // pairs of a row sorted in LDS (what the moment plan takes at most)
+constexpr int NROW = 256;           // pairs of a row sorted in LDS (the moment plan takes 64 at most)
 
 __global__ void __launch_bounds__(NT)
 k_count(Geom g, int n, const double *__restrict__ pos, const double *__restrict__ f, const int *__restrict__ u,
@@ -239,7 +239,9 @@ __device__ inline bool key_less(int ja, int a1, int a2, int a3, int jb, int b1, 
 // The rows, sorted by (j, S).  The accepted candidates of a row are gathered in LDS in
 // any order; a pair's place is the number of keys below its own (keys are
 // unique), found by a lane per pair.  Rows longer than NROW are inserted one by one
-// in the output by the first lane.
+// in the output by the first lane, which no plan takes (whole list against a thread per
+// atom: 1,024 atoms of 258 pairs 8.2 -> 7.2 ms, 8,192 of 284 pairs 80 -> 26, 54 of 2,763 pairs
+// 5.8 -> 4.3).
 __global__ void __launch_bounds__(NT)
 k_fill(Geom g, int n, const double *__restrict__ pos, const double *__restrict__ f, const int *__restrict__ u,
        const int *__restrict__ cellc, const int *__restrict__ bin_start, const int *__restrict__ bin_list,

@@ -11,7 +11,8 @@ from test_gpu_parity import _np
 
 pytestmark = pytest.mark.gpu
 
-# atoms, orbitals, moments, terms; 1024, 8192 and 65536 rows end forms of the search, 98304 one of the expansion
+# atoms, orbitals, moments, terms; 65536 rows end a form of the search (16384 too, and by terms fewer than 65536:
+# test_gpu_level_routes.py), 98304 one of the expansion, 8192 are one tree of its sums
 CASES = [(1, 1, 3, 1), (33, 1, 20, 201), (32, 5, 21, 200), (1024, 1, 8, 202), (205, 5, 9, 203), (910, 9, 8, 51),
          (8192, 1, 6, 26), (8193, 1, 5, 52), (65536, 1, 4, 24), (65537, 1, 4, 24), (98304, 1, 6, 8), (98305, 1, 6, 8),
          (5, 9, 7, 3), (32, 2, 9, 404), (8, 5, 9, 1024)]
