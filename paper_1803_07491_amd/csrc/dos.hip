@@ -535,8 +535,8 @@ k_bracket_pick(int n_rows, unsigned n_blocks, const double *__restrict__ part, F
 //    a closing pass's nodes miss its turn.
 // Four passes then do for what bisection alone takes 15 for.  Against it the level is
 // within 1e-15 eV over 54 to 27,648 atoms and 1 to 1024 terms; whole tails, 200 terms: 128
-// atoms 168 -> 130 us, 2000 atoms 326 -> 177, 8192 atoms 590 -> 308, 128,000 atoms 6.16 ->
-// 2.15 ms; bisected throughout (a gap) 1000 rows take 210 us.
+// atoms 168 -> 124 us, 2000 atoms 326 -> 180, 8192 atoms 590 -> 289, 128,000 atoms 6.16 ->
+// 2.10 ms; bisected throughout (a gap) 1000 rows take 208 us.
 constexpr int FT_MAX_HALVINGS = 64;            // as many as plain bisection takes at most
 constexpr int FT_LEVELS = 4, FT_NODES = (1 << FT_LEVELS) - 1;
 constexpr int FT_TREE = 3, FT_CLOSE = 2;       // bisecting passes first, closing passes then

@@ -957,8 +957,8 @@ constexpr int HL_PAIRS = 16;
 
 // The same step (k_step: rows, sums and their order are its own) for FP32, and for
 // vectors stored in FP16 (S).  What bounds it is the traffic between L2 and memory
-// (about 3.7 TB/s in every variant) and, for s,p,d, the rate of L1 accesses; so the
-// products leave the VALU (60% busy before, 27% now), and what a wave waits for is
+// (3.9 TB/s, 128,000 atoms) and, for s,p,d, the rate of L1 accesses; so the
+// products leave the VALU (59% busy before, 29% now), and what a wave waits for is
 // asked for early: a row's records two rows ahead, its vectors before the stores of
 // the row before it.  Against products on the VALU from LDS copies of the blocks,
 // 18 moments: s,p,d Lanczos, 6,912 atoms 95.3 -> 68.6 ms; FP16 rows, 2,048 atoms
