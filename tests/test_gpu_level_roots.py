@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import oracle as O
+import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -58,3 +59,26 @@ def test_root_is_bisections(bop, R, scale):
         # is 1e-12 of the counts, and moves a root by 1e-12 of the band
         assert abs(got - want) <= 1e-11 * width, (t, got, want)
     assert several >= 5
+
+
+@pytest.mark.parametrize("n_max", [20, 21])
+def test_root_of_a_count_that_few_rows_stretch(bop, n_max):
+    """BF16 moments of so high an order: some rows' bands are a thousand times the
+    others', so that a 4096th of the band holds all of most rows' states, and the count
+    there rises and falls."""
+    n_exp = 60
+    pos, cell = W.cubic_lattice("bcc", 2.9, 4)
+    pos = W.displace(pos, cell, 0.05, np.random.default_rng(1))
+    model = W.canonical_d_model(3.5)
+    p = bop.EnergyPath(pos, cell, np.zeros(len(pos), np.int32), model, n_max, n_exp, "bf16")
+    p.run_moments()
+    bop.recursion(p.mu, n_max, out=p.rec)
+    rec = {k: v.cpu().numpy() for k, v in p.rec.items()}
+    gs = O.dos_coeffs(p.mu.cpu().numpy().reshape(-1, n_max + 1), rec, n_max, n_exp)
+    width = (rec["a_inf"] + 2 * rec["b_inf"]).max() - (rec["a_inf"] - 2 * rec["b_inf"]).min()
+    assert width > 100 * np.median(4 * rec["b_inf"])
+    for fill in np.linspace(0.1, 1.9, 37):
+        want = O.fermi(gs, rec["a_inf"], rec["b_inf"], fill * len(gs))
+        got = float(bop.energy(p.mu, p.rec, p.H_on, fill * len(gs), n_max, n_exp)["E_F"].cpu()[0])
+        # the expansions of such moments carry 1e-9 of their rounding; the roots lie 0.1 apart
+        assert abs(got - want) <= 1e-6, (fill, got, want)
